@@ -992,6 +992,9 @@ template <class MT>
 __device__ inline typename FragT<MT>::type wfrag_global(const MT* W, int n_out, int n_in, int ld, int m, int kb,
                                                         int lane) {
   typedef MT v4 __attribute__((ext_vector_type(4)));
+  // (a laundered pointer has lost its address space: without the cast the
+  // loads would be flat ones, which also wait on the LDS counter)
+  typedef const __attribute__((address_space(1))) v4* gptr;
   typename FragT<MT>::type a;
   const int row = 16 * m + (lane & 15), g = lane >> 4;
   const bool rok = row < n_out;
@@ -1000,7 +1003,7 @@ __device__ inline typename FragT<MT>::type wfrag_global(const MT* W, int n_out, 
     const int col = 32 * kb + 16 * h + 4 * g;
     v4 v;
     if (rok && col < n_in) {
-      v = *reinterpret_cast<const v4*>(W + (int64_t)row * ld + col);
+      v = *(gptr)(W + (int64_t)row * ld + col);
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = from_f32<MT>(0.0f);
@@ -1077,13 +1080,21 @@ __device__ inline void wave_lds_sync() {
 // XCD-aware work split: workgroups are dispatched round-robin over the 8
 // XCDs, so workgroup b runs on XCD b % 8. Each XCD takes one contiguous range
 // of tiles (neighbouring queries share nodes and texels, and each XCD has
-// its own L2); inside it the workers stride through the range.
+// its own L2); inside it the workers stride through the range. With no more
+// tiles than workers every worker takes one, the workgroups first, so a
+// small batch runs on as many CUs as it has tiles.
 struct TileRange {
   int64_t first, end, stride;
 };
 __device__ inline TileRange xcd_tiles(int64_t n_tiles, int workers_per_wg, int worker) {
   const int G = gridDim.x;
   TileRange r;
+  if (n_tiles <= (int64_t)G * workers_per_wg) {
+    r.first = (int64_t)worker * G + blockIdx.x;
+    r.end = n_tiles;
+    r.stride = (int64_t)G * workers_per_wg;
+    return r;
+  }
   if (G % 8 != 0 || G < 8) {
     r.first = (int64_t)blockIdx.x * workers_per_wg + worker;
     r.end = n_tiles;

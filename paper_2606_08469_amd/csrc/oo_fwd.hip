@@ -1,10 +1,10 @@
-// Forward kernels: standalone encoding, standalone decoder, the fused
-// encode + decode query, the residual assembly with its FP64 loss
+// Forward kernels: standalone encoding, the fused encode + decode query, the residual assembly with its FP64 loss
 // reduction, and the FP32 -> FP16/BF16 parameter cast.
 #include <hip/hip_runtime.h>
 
 #include "oo_device.h"
 #include "oo_internal.h"
+#include "oo_mlp.h"
 
 namespace oo {
 
@@ -81,162 +81,6 @@ __global__ __launch_bounds__(256) void encode_kernel(const TreeArgs T, const flo
 }
 
 // ---------------------------------------------------------------------------
-// Decoder forward on one wave's 64-query activation tile.
-// ---------------------------------------------------------------------------
-
-// Weight fragments: packed in LDS in fragment order (zero padded), or read
-// straight from the row-major matrices. Packed layout: layer 0 first
-// ((H/16) x KB0 fragments), then each hidden layer ((H/16) x (H/32)), then
-// the output layer (H/32); one fragment is 64 lanes x 8 elements.
-template <class MT, bool WLDS>
-struct WFrag {
-  const MT* lds;
-  int KB0;
-  __device__ inline typename FragT<MT>::type get(const MlpArgs& M, int layer, int m, int kb, int lane) const {
-    if constexpr (WLDS) {
-      const int MH = M.H / 16, KH = M.H / 32;
-      int base, KB;
-      if (layer == 0) {
-        base = 0;
-        KB = KB0;
-      } else {
-        base = MH * KB0 + (layer - 1) * MH * KH;
-        KB = KH;
-      }
-      return *reinterpret_cast<const typename FragT<MT>::type*>(lds + ((base + m * KB + kb) * kWave + lane) * 8);
-    } else {
-      const int n_in = layer == 0 ? M.K0 : M.H;
-      const int n_out = layer == M.n_layers - 1 ? M.n_out : M.H;
-      return wfrag_global<MT>(launder_ptr(reinterpret_cast<const MT*>(M.W[layer])), n_out, n_in, n_in, m, kb, lane);
-    }
-  }
-};
-
-__device__ inline f32x4 bias_tile(const float* b, int n_out, int m, int lane) {
-  f32x4 v;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 16 * m + 4 * (lane >> 4) + j;
-    v[j] = row < n_out ? b[row] : 0.0f;
-  }
-  return v;
-}
-
-// Runs the MLP on N-tiles t0 .. t0+NT-1 of the activation tile and returns
-// the output tile per N-tile (rows 0..2 = RGB in lanes 0..15).
-template <class MT, int H, int NT, class WSrc>
-__device__ inline void mlp_forward_tiles(const MlpArgs& M, const WSrc& W, const MT* htile, int KB0, int t0,
-                                         int lane, f32x4 out[NT]) {
-  // M is a kernel argument: indexing its arrays reads the argument segment.
-  typedef typename FragT<MT>::type frag;
-  constexpr int MH = H / 16, KH = H / 32;
-  f32x4 acc[MH][NT];
-  // layer 0: K0 -> H
-#pragma unroll
-  for (int m = 0; m < MH; ++m) {
-    const f32x4 bt = bias_tile(M.b[0], H, m, lane);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[m][t] = bt;
-  }
-  // Each K-chunk's weight fragments are all read before its MFMAs, so their
-  // LDS latency overlaps instead of stalling every pair of MFMAs.
-  for (int kb = 0; kb < KB0; ++kb) {
-    frag bf[NT], a[MH];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) bf[t] = htile_get<MT>(htile, KB0, t0 + t, kb, lane);
-#pragma unroll
-    for (int m = 0; m < MH; ++m) a[m] = W.get(M, 0, m, kb, lane);
-    __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink each read to its MFMAs)
-#pragma unroll
-    for (int m = 0; m < MH; ++m)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[m][t] = mma(a[m], bf[t], acc[m][t]);
-  }
-  // hidden layers H -> H
-  for (int layer = 1; layer < M.n_layers - 1; ++layer) {
-    frag bf[KH][NT];
-#pragma unroll
-    for (int kb = 0; kb < KH; ++kb)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) bf[kb][t] = chain_frag<MT>(acc[2 * kb][t], acc[2 * kb + 1][t], true);
-#pragma unroll
-    for (int m = 0; m < MH; ++m) {
-      const f32x4 bt = bias_tile(M.b[layer], H, m, lane);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[m][t] = bt;
-    }
-#pragma unroll
-    for (int kb = 0; kb < KH; ++kb) {
-      frag a[MH];
-#pragma unroll
-      for (int m = 0; m < MH; ++m) a[m] = W.get(M, layer, m, kb, lane);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int m = 0; m < MH; ++m)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[m][t] = mma(a[m], bf[kb][t], acc[m][t]);
-    }
-  }
-  // output layer H -> 3
-  const int lo = M.n_layers - 1;
-  const f32x4 bt = bias_tile(M.b[lo], M.n_out, 0, lane);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) out[t] = bt;
-#pragma unroll
-  for (int kb = 0; kb < KH; ++kb) {
-    const frag a = W.get(M, lo, 0, kb, lane);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) out[t] = mma(a, chain_frag<MT>(acc[2 * kb][t], acc[2 * kb + 1][t], true), out[t]);
-  }
-}
-
-// Packs every layer's weights into LDS in fragment order (zero padded).
-template <class MT>
-__device__ inline void pack_weights_lds(const MlpArgs& M, MT* lds) {
-  int offset = 0;
-  for (int layer = 0; layer < M.n_layers; ++layer) {
-    const int n_in = layer == 0 ? M.K0 : M.H;
-    const int n_out = layer == M.n_layers - 1 ? 3 : M.H;
-    const int KB = (n_in + 31) / 32;
-    const int total = ((n_out + 15) / 16) * KB * kWave * 8;
-    const MT* src = reinterpret_cast<const MT*>(M.W[layer]);
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
-      const int i = e & 7, lane = (e >> 3) & 63, frag = e >> 9;
-      const int kb = frag % KB, m = frag / KB;
-      const int row = 16 * m + (lane & 15), col = nu(kb, lane >> 4, i);
-      lds[offset + e] = (row < n_out && col < n_in) ? src[(int64_t)row * n_in + col] : from_f32<MT>(0.0f);
-    }
-    offset += total;
-  }
-}
-
-template <class MT>
-__host__ __device__ inline int packed_weight_elems(int n_layers, int K0, int H) {
-  int total = 0;
-  for (int layer = 0; layer < n_layers; ++layer) {
-    const int n_in = layer == 0 ? K0 : H;
-    const int n_out = layer == n_layers - 1 ? 3 : H;
-    total += ((n_out + 15) / 16) * ((n_in + 31) / 32) * kWave * 8;
-  }
-  return total;
-}
-
-template <class MT, int NT>
-__device__ inline void store_rgb(const f32x4 out[NT], int t0, int64_t q_base, int64_t Q, int lane, float* rgb) {
-  if (lane < 16) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int64_t q = q_base + 16 * (t0 + t) + lane;
-      if (q < Q) {
-        rgb[3 * q + 0] = out[t][0];
-        rgb[3 * q + 1] = out[t][1];
-        rgb[3 * q + 2] = out[t][2];
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Fused query: encode 64 queries per wave into LDS, decode them there.
 // ---------------------------------------------------------------------------
 // Queries q < n_idx also store their node index per level in idx_out
@@ -263,8 +107,10 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
   const int KB0 = (M.K0 + 31) / 32;
   const int wl_elems = WLDS ? packed_weight_elems<MT>(M.n_layers, M.K0, M.H) : 0;
-  MT* wl = reinterpret_cast<MT*>(smem);
+  float* const bias = reinterpret_cast<float*>(smem);
+  MT* wl = reinterpret_cast<MT*>(bias + bias_floats(M.n_layers, H));
   MT* htile = wl + wl_elems + wave * (4 * KB0 * kWave * 8);
+  load_biases_lds(M, bias);
   if (WLDS) pack_weights_lds<MT>(M, wl);
   {  // zero the K padding of this lane's row once
     const float z[4] = {0.f, 0.f, 0.f, 0.f};
@@ -315,109 +161,9 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
 #pragma unroll
     for (int t0 = 0; t0 < 4; t0 += NT) {
       f32x4 out[NT];
-      mlp_forward_tiles<MT, H, NT>(M, W, htile, KB0, t0, lane, out);
-      store_rgb<MT, NT>(out, t0, tile * 64, Q, lane, rgb);
-    }
-    wave_lds_sync();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Standalone decoder: h rows from memory into the LDS tile, then decode.
-// ---------------------------------------------------------------------------
-template <class MT, int H, bool WLDS>
-__global__ __launch_bounds__(512) void mlp_kernel(const MlpArgs M, const MT* __restrict__ h, int64_t Q,
-                                                  float* __restrict__ rgb) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  // N-tiles per pass: with 16-bit operands and the weights in LDS all
-  // four, so that each weight fragment read serves four MFMAs (the other
-  // variants would spill)
-  constexpr int NT = sizeof(MT) == 2 && WLDS ? 4 : 2;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  const int KB0 = (M.K0 + 31) / 32;
-  const int wl_elems = WLDS ? packed_weight_elems<MT>(M.n_layers, M.K0, M.H) : 0;
-  MT* wl = reinterpret_cast<MT*>(smem);
-  MT* htile = wl + wl_elems + wave * (4 * KB0 * kWave * 8);
-  if (WLDS) pack_weights_lds<MT>(M, wl);
-  {
-    const float z[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k = M.K0; k < 32 * KB0; k += 4) htile_put4<MT>(htile, KB0, lane, k, z);
-  }
-  __syncthreads();
-  const WFrag<MT, WLDS> W{wl, KB0};
-  const int64_t n_tiles = (Q + 63) / 64;
-  const TileRange tr = xcd_tiles(n_tiles, waves, wave);
-  // 16-bit rows: a tile's rows are P pieces of 16 bytes each; this lane
-  // reads pieces lane + 64 i, i = 0 .. P-1, walked by row and position
-  // without a division per piece
-  constexpr int EP = 16 / sizeof(MT);
-  const int P = M.K0 / EP > 0 ? M.K0 / EP : 1;
-  const int step_r = 64 / P, step_m = 64 % P;
-  const int lane_r = lane / P, lane_m = lane % P;
-  for (int64_t tile = tr.first; tile < tr.end; tile += tr.stride) {
-    // With 16-bit rows the wave reads the tile's 64 contiguous rows as
-    // 16-byte pieces in order (coalesced; EP entries each, K0 a multiple of
-    // EP), eight of a lane's pieces (at most 16, K0 <= 128) loaded before
-    // any of them is stored, so their latencies overlap; the pieces go to
-    // their fragment slots unconverted. Otherwise each lane reads its own
-    // row four entries at a time (FP32 measured faster that way).
-    const int64_t q0 = tile * 64;
-    const int nrow = Q - q0 < 64 ? (int)(Q - q0) : 64;
-    if (sizeof(MT) == 2 && M.K0 % EP == 0) {
-      typedef MT vP __attribute__((ext_vector_type(EP)));
-      typedef MT v4 __attribute__((ext_vector_type(4)));
-      constexpr int kMaxPieces = 128 / EP, kBatch = 8;
-      const vP* src = reinterpret_cast<const vP*>(h + q0 * (int64_t)M.K0);
-      int r = lane_r, m = lane_m;  // row and position of piece lane + 64 i
-#pragma unroll 1
-      for (int i0 = 0; i0 < kMaxPieces; i0 += kBatch) {
-        vP xs[kBatch];
-        int rs[kBatch], ms[kBatch];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-          const int i = i0 + j;
-          rs[j] = r;
-          ms[j] = m;
-          xs[j] = vP{};
-          if (i < P && r < nrow) xs[j] = src[lane + 64 * i];
-          m += step_m;
-          r += step_r;
-          if (m >= P) {
-            m -= P;
-            ++r;
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-          if (i0 + j < P) {
-#pragma unroll
-            for (int c = 0; c < EP; c += 4) {
-              const v4 x4 = {xs[j][c], xs[j][c + 1], xs[j][c + 2], xs[j][c + 3]};
-              *reinterpret_cast<v4*>(htile + htile_index<MT>(rs[j], ms[j] * EP + c, KB0)) = x4;
-            }
-          }
-        }
-      }
-    } else {
-      typedef MT v4 __attribute__((ext_vector_type(4)));
-      const int64_t q = q0 + lane;
-      const v4* row = reinterpret_cast<const v4*>(h + (q < Q ? q : 0) * (int64_t)M.K0);
-      for (int k = 0; k < M.K0; k += 4) {
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        if (q < Q) {
-          const v4 r = row[k >> 2];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) v[c] = to_f32(r[c]);
-        }
-        htile_put4<MT>(htile, KB0, lane, k, v);
-      }
-    }
-    wave_lds_sync();
-#pragma unroll
-    for (int t0 = 0; t0 < 4; t0 += NT) {
-      f32x4 out[NT];
-      mlp_forward_tiles<MT, H, NT>(M, W, htile, KB0, t0, lane, out);
-      store_rgb<MT, NT>(out, t0, tile * 64, Q, lane, rgb);
+      mlp_forward_tiles<MT, H, NT, 0>(
+          M, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<MT>(htile, KB0, t0 + t, kb, lane); }, out);
+      store_rgb<NT>(out, tile * 64 + 16 * t0, Q, lane, rgb);
     }
     wave_lds_sync();
   }
@@ -497,24 +243,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C == 4 ? 4 
 // Packs the predictor's FP32 weights into LDS in fragment order, split into
 // BF16 hi (at hi) and lo (at hi + the packed size) parts.
 __device__ inline void pack_weights_split(const MlpArgs& M, bf16* hi, int total_elems) {
-  int offset = 0;
-  for (int layer = 0; layer < M.n_layers; ++layer) {
-    const int n_in = layer == 0 ? M.K0 : M.H;
-    const int n_out = layer == M.n_layers - 1 ? M.n_out : M.H;
-    const int KB = (n_in + 31) / 32;
-    const int total = ((n_out + 15) / 16) * KB * kWave * 8;
-    const float* src = static_cast<const float*>(M.W[layer]);
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
-      const int i = e & 7, lane = (e >> 3) & 63, frag = e >> 9;
-      const int kb = frag % KB, m = frag / KB;
-      const int row = 16 * m + (lane & 15), col = nu(kb, lane >> 4, i);
-      const float w = (row < n_out && col < n_in) ? src[(int64_t)row * n_in + col] : 0.0f;
-      const bf16 h = from_f32<bf16>(w);
-      hi[offset + e] = h;
-      hi[total_elems + offset + e] = from_f32<bf16>(w - to_f32(h));
+  pack_layers<float>(M, [&](int f, int lane, const f32x8& w) {
+    bf16x8 h, l;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      h[i] = from_f32<bf16>(w[i]);
+      l[i] = from_f32<bf16>(w[i] - to_f32(h[i]));
     }
-    offset += total;
-  }
+    reinterpret_cast<bf16x8*>(hi)[f * kWave + lane] = h;
+    reinterpret_cast<bf16x8*>(hi + total_elems)[f * kWave + lane] = l;
+  });
 }
 
 __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& h, bf16x8& l) {
@@ -543,12 +281,13 @@ __device__ __forceinline__ f32x4 mma_split(const bf16x8& ah, const bf16x8& al, c
 static_assert(kDispK == 36, "the predictor's input is 32 hash features, the unit direction and a zero");
 template <int NT>
 __device__ inline void disp_mlp_split(const MlpArgs& M, const WFrag<bf16, true>& Wh, const WFrag<bf16, true>& Wl,
-                                      const float* htile, const float u[3], int t0, int lane, f32x4 out[NT]) {
+                                      const float* bias, const float* htile, const float u[3], int t0, int lane,
+                                      f32x4 out[NT]) {
   constexpr int MH = kDispH / 16, KH = kDispH / 32;
   f32x4 acc[MH][NT];
 #pragma unroll
   for (int m = 0; m < MH; ++m) {
-    const f32x4 bt = bias_tile(M.b[0], kDispH, m, lane);
+    const f32x4 bt = bias_tile(bias, m, lane);
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[m][t] = bt;
   }
@@ -604,7 +343,7 @@ __device__ inline void disp_mlp_split(const MlpArgs& M, const WFrag<bf16, true>&
       for (int t = 0; t < NT; ++t) chain(kb, t, bh[kb][t], bl[kb][t]);
 #pragma unroll
     for (int m = 0; m < MH; ++m) {
-      const f32x4 bt = bias_tile(M.b[layer], kDispH, m, lane);
+      const f32x4 bt = bias_tile(bias + layer * kDispH, m, lane);
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[m][t] = bt;
     }
@@ -624,7 +363,7 @@ __device__ inline void disp_mlp_split(const MlpArgs& M, const WFrag<bf16, true>&
     }
   }
   const int lo = M.n_layers - 1;
-  const f32x4 bo = bias_tile(M.b[lo], M.n_out, 0, lane);
+  const f32x4 bo = bias_tile(bias + lo * kDispH, 0, lane);
 #pragma unroll
   for (int t = 0; t < NT; ++t) out[t] = bo;
 #pragma unroll
@@ -648,14 +387,16 @@ __global__ __launch_bounds__(256) void disparity_fwd_kernel(const DispArgs G, co
   const int KB0 = (P.K0 + 31) / 32;
   const int KBT = SPLIT ? 1 : KB0;  // K-chunks the FP32 tile holds
   const int wl_elems = SPLIT ? packed_weight_elems<bf16>(P.n_layers, P.K0, P.H) : 0;
-  bf16* const wl = reinterpret_cast<bf16*>(smem);
+  float* const bias = reinterpret_cast<float*>(smem);
+  bf16* const wl = reinterpret_cast<bf16*>(bias + bias_floats(P.n_layers, kDispH));
   float* const htile = reinterpret_cast<float*>(wl + 2 * wl_elems) + wave * (4 * KBT * kWave * 8);
+  load_biases_lds(P, bias);
   if (SPLIT) pack_weights_split(P, wl, wl_elems);
   {  // zero the K padding of this lane's row once
     const float z[4] = {0.f, 0.f, 0.f, 0.f};
     for (int k = P.K0; k < 32 * KBT; k += 4) htile_put4<float>(htile, KBT, lane, k, z);
   }
-  if (SPLIT) __syncthreads();
+  __syncthreads();
   const WFrag<float, false> W{nullptr, KB0};
   const WFrag<bf16, true> Wh{wl, KB0}, Wlo{wl + wl_elems, KB0};
   const int64_t n_tiles = (Q + 63) / 64;
@@ -674,9 +415,10 @@ __global__ __launch_bounds__(256) void disparity_fwd_kernel(const DispArgs G, co
     for (int t0 = 0; t0 < 4; t0 += NT) {
       f32x4 out[NT];
       if constexpr (SPLIT)
-        disp_mlp_split<NT>(P, Wh, Wlo, htile, u, t0, lane, out);
+        disp_mlp_split<NT>(P, Wh, Wlo, bias, htile, u, t0, lane, out);
       else
-        mlp_forward_tiles<float, kDispH, NT>(P, W, htile, KB0, t0, lane, out);
+        mlp_forward_tiles<float, kDispH, NT, (kDispK + 31) / 32>(
+            P, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<float>(htile, KB0, t0 + t, kb, lane); }, out);
       if (lane < 16) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -828,28 +570,6 @@ __global__ __launch_bounds__(256) void saved_nodes_kernel(const int32_t* __restr
 // Launchers
 // ---------------------------------------------------------------------------
 
-static int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    hipGetDevice(&dev);
-    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (cus <= 0) cus = 256;
-  }
-  return cus;
-}
-
-static int max_lds() {
-  static int lds = 0;
-  if (!lds) {
-    int dev = 0;
-    hipGetDevice(&dev);
-    hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    if (lds <= 0) lds = 65536;
-  }
-  return lds;
-}
-
 template <class TT, class HT, int C>
 static hipError_t launch_encode_t(const TreeArgs& T, const float* x, const float* d, int64_t B, void* h,
                                   int32_t* idx, const DispArgs& G, hipStream_t st) {
@@ -890,13 +610,13 @@ hipError_t launch_encode(const TreeArgs& T, oo_dtype td, const float* x, const f
 }
 
 // Grid of the tile kernels for a workgroup of `waves` waves using lds bytes.
-static int tile_grid(int64_t Q, int waves, size_t lds) {
-  const int64_t n_tiles = (Q + 63) / 64;
+// One workgroup per tile up to the resident count, so that a small batch
+// spreads over the chip (xcd_tiles hands out the tiles to match).
+static int tile_grid(int64_t n_tiles, size_t lds) {
   // LDS per CU on gfx950 is 160 KiB: one or two workgroups fit per CU.
   const int per_cu = lds * 2 <= (size_t)160 * 1024 ? 2 : 1;
   int64_t g = (int64_t)device_cus() * per_cu;
-  const int64_t need = (n_tiles + waves - 1) / waves;
-  if (g > need) g = need;
+  if (g > n_tiles) g = n_tiles;
   if (g >= 8) g -= g % 8;
   return (int)(g > 0 ? g : 1);
 }
@@ -906,10 +626,11 @@ template <class MT>
 static void tile_launch_shape_plain(const MlpArgs& M, int64_t Q, int& waves, size_t& lds, int& grid) {
   const int KB0 = (M.K0 + 31) / 32;
   const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
+  const size_t bb = bias_bytes(M);
   waves = 8;
-  while (waves > 1 && waves * tile_bytes > (size_t)max_lds()) --waves;
-  lds = waves * tile_bytes;
-  grid = tile_grid(Q, waves, lds);
+  while (waves > 1 && bb + waves * tile_bytes > (size_t)max_lds()) --waves;
+  lds = bb + waves * tile_bytes;
+  grid = tile_grid((Q + 63) / 64, lds);
 }
 
 // Workgroup shape for the tile kernels: up to 8 waves, each with a 64-query
@@ -919,7 +640,8 @@ static void tile_launch_shape(const MlpArgs& M, int64_t Q, bool& wlds, int& wave
   const int KB0 = (M.K0 + 31) / 32;
   const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
   const size_t wbytes = (size_t)packed_weight_elems<MT>(M.n_layers, M.K0, M.H) * sizeof(MT);
-  const size_t cap = (size_t)max_lds();
+  const size_t bb = bias_bytes(M);
+  const size_t cap = (size_t)max_lds() - bb;
   waves = 8;
   wlds = true;
   while (waves > 4 && wbytes + waves * tile_bytes > cap) --waves;
@@ -928,8 +650,8 @@ static void tile_launch_shape(const MlpArgs& M, int64_t Q, bool& wlds, int& wave
     waves = 8;
     while (waves > 1 && waves * tile_bytes > cap) --waves;
   }
-  lds = (wlds ? wbytes : 0) + waves * tile_bytes;
-  grid = tile_grid(Q, waves, lds);
+  lds = bb + (wlds ? wbytes : 0) + waves * tile_bytes;
+  grid = tile_grid((Q + 63) / 64, lds);
 }
 
 
@@ -983,31 +705,6 @@ hipError_t launch_query(const TreeArgs& T, oo_dtype td, const MlpArgs& M, oo_dty
   return T.C == 4 ? launch_query_c<bf16, bf16, 4>(T, M, src, Q, rgb, O, G, st)
                   : launch_query_c<bf16, bf16, 8>(T, M, src, Q, rgb, O, G, st);
   (void)md;
-}
-
-template <class MT, int H>
-static hipError_t launch_mlp_t(const MlpArgs& M, const void* h, int64_t Q, float* rgb, hipStream_t st) {
-  bool wlds;
-  int waves, grid;
-  size_t lds;
-  tile_launch_shape<MT>(M, Q, wlds, waves, lds, grid);
-  if (wlds) {
-    auto k = mlp_kernel<MT, H, true>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, M, reinterpret_cast<const MT*>(h), Q, rgb);
-  } else {
-    auto k = mlp_kernel<MT, H, false>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, M, reinterpret_cast<const MT*>(h), Q, rgb);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_mlp(const MlpArgs& M, oo_dtype md, const void* h, int64_t Q, float* rgb, hipStream_t st) {
-  if (Q == 0) return hipSuccess;
-  if (md == OO_F32) return M.H == 64 ? launch_mlp_t<float, 64>(M, h, Q, rgb, st) : launch_mlp_t<float, 128>(M, h, Q, rgb, st);
-  if (md == OO_F16) return M.H == 64 ? launch_mlp_t<f16, 64>(M, h, Q, rgb, st) : launch_mlp_t<f16, 128>(M, h, Q, rgb, st);
-  return M.H == 64 ? launch_mlp_t<bf16, 64>(M, h, Q, rgb, st) : launch_mlp_t<bf16, 128>(M, h, Q, rgb, st);
 }
 
 static int combine_group(int N) {
@@ -1095,8 +792,8 @@ hipError_t launch_disparity_fwd(const DispArgs& G, oo_dtype md, const QuerySrc& 
   constexpr int waves = 4;
   const size_t wbytes = split ? (size_t)2 * packed_weight_elems<bf16>(P.n_layers, P.K0, P.H) * sizeof(bf16) : 0;
   const int kbt = split ? 1 : (P.K0 + 31) / 32;
-  const size_t lds = wbytes + (size_t)waves * 4 * kbt * kWave * 8 * sizeof(float);
-  const int grid = tile_grid(Q, waves, lds);
+  const size_t lds = bias_bytes(P) + wbytes + (size_t)waves * 4 * kbt * kWave * 8 * sizeof(float);
+  const int grid = tile_grid((Q + 63) / 64, lds);
   if (split) {
     hipFuncSetAttribute((const void*)disparity_fwd_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(disparity_fwd_kernel<true>, dim3(grid), dim3(64 * waves), lds, st, G, P, src, Q, d_out);

@@ -48,6 +48,10 @@ struct ReduceDst {
   float* dst[2 * kMaxLayers];
 };
 
+// Compute units of the device, and the LDS a workgroup may use.
+int device_cus();
+int max_lds();
+
 hipError_t launch_encode(const TreeArgs& T, oo_dtype td, const float* x, const float* d, int64_t B, void* h,
                          oo_dtype hd, int32_t* idx, const DispArgs& G, hipStream_t st);
 hipError_t launch_mlp(const MlpArgs& M, oo_dtype md, const void* h, int64_t Q, float* rgb, hipStream_t st);
