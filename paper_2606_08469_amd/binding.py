@@ -96,6 +96,8 @@ def lib():
         L.oo_query_fwd.argtypes = [vp, vp, vp, vp, vp, i64, vp, vp]
         L.oo_residual_workspace_bytes.argtypes = [vp, vp, vp, C.POINTER(C.c_size_t)]
         sz = C.c_size_t
+        L.oo_query_workspace_bytes.argtypes = [vp, vp, i64, C.POINTER(C.c_size_t)]
+        L.oo_query_fwd_ws.argtypes = [vp, vp, vp, vp, vp, i64, vp, vp, sz, vp]
         L.oo_radiosity_residual_fwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.oo_radiosity_residual_bwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.oo_cast_params.argtypes = [vp, vp, i32, i64, vp]
@@ -110,6 +112,7 @@ def lib():
         L.oo_profile_kind_name.restype = C.c_char_p
         L.oo_last_error.restype = C.c_char_p
         for f in ("oo_build_octree", "oo_encode_query", "oo_mlp_fwd", "oo_query_fwd",
+                  "oo_query_workspace_bytes", "oo_query_fwd_ws",
                   "oo_residual_workspace_bytes", "oo_radiosity_residual_fwd", "oo_radiosity_residual_bwd",
                   "oo_cast_params", "oo_profile_begin", "oo_profile_end", "oo_residual_node_indices",
                   "oo_dot_f64", "oo_dot_f64_noalloc", "oo_adam_step", "oo_touched_nodes"):
@@ -318,6 +321,13 @@ def query_fwd(tree: Tree, mlp: MLP, x, d, feat=None, W=None, out=None, attr=None
     B = x.shape[0]
     rgb = torch.empty((B, 3), dtype=torch.float32, device="cuda") if out is None else out
     ts, ms = tree.struct(feat), mlp.struct(W)
+    if tree.disparity is not None:  # the split kernels, with a workspace from torch's allocator
+        n = C.c_size_t(0)
+        _check(lib().oo_query_workspace_bytes(C.byref(ts), C.byref(ms), B, C.byref(n)), "oo_query_workspace_bytes")
+        ws = torch.empty(max(n.value, 256), dtype=torch.uint8, device="cuda")
+        _check(lib().oo_query_fwd_ws(C.byref(ts), C.byref(ms), _ptr(x), _ptr(d), _ptr(attr), B, _ptr(rgb), _ptr(ws),
+                                     _nbytes(ws), _stream()), "oo_query_fwd_ws")
+        return rgb
     _check(lib().oo_query_fwd(C.byref(ts), C.byref(ms), _ptr(x), _ptr(d), _ptr(attr), B, _ptr(rgb), _stream()),
            "oo_query_fwd")
     return rgb

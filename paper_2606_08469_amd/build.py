@@ -13,13 +13,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liboctaoctree.so")
-SOURCES = ["oo_api.cpp", "oo_fwd.hip", "oo_mlp.hip", "oo_bwd.hip", "oo_sort.hip", "oo_optim.hip", "oo_disp.hip"]
+SOURCES = ["oo_api.cpp", "oo_fwd.hip", "oo_mlp.hip", "oo_pred.hip", "oo_bwd.hip", "oo_sort.hip", "oo_optim.hip", "oo_disp.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-result",
+    "-Wall", "-Wno-unused-result", "-Wno-unused-value",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 

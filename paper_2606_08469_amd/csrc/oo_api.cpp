@@ -269,7 +269,42 @@ int check_attrs(const oo_residual_batch* b, const ResidualArgs& A, const MlpArgs
   return OO_OK;
 }
 
+int check_query(const oo_tree* tree, const oo_mlp* mlp, const float* x, const float* dir, const float* attr, int64_t B,
+                const float* rgb_out, TreeArgs& T, MlpArgs& M, DispArgs& G) {
+  int rc = check_tree(tree, T);
+  if (rc) return rc;
+  if ((rc = check_mlp(mlp, tree->n_levels * tree->C, M))) return rc;
+  if ((rc = check_pair(tree, mlp))) return rc;
+  if ((rc = check_disparity(tree, G, false))) return rc;
+  if (B < 0) return fail(OO_EINVAL, "B must be >= 0");
+  if (B == 0) return OO_OK;
+  if (!x || !dir || !rgb_out) return fail(OO_EINVAL, "x, dir and rgb_out are required");
+  if (M.E > 0 && !attr) return fail(OO_EINVAL, "attr is required: the decoder reads %d surface attributes", M.E);
+  return OO_OK;
+}
+
+// Queries q0 .. q0 + n - 1 of a caller's arrays.
+QuerySrc query_src(const float* x, const float* dir, const float* attr, int64_t q0, int64_t n, const MlpArgs& M) {
+  QuerySrc src{x + 3 * q0, dir + 3 * q0, n, x + 3 * q0, dir + 3 * q0};
+  src.gA = src.gB = attr ? attr + (int64_t)M.E * q0 : nullptr;
+  src.E = M.E;
+  return src;
+}
+
+// Queries of one pass of the split query: the batch in equal passes of at
+// most 2^20, whole tiles each.
+int64_t query_pass(int64_t B) {
+  const int64_t passes = (B + (int64_t(1) << 20) - 1) >> 20;
+  return passes > 0 ? ((B + passes - 1) / passes + 63) / 64 * 64 : 0;
+}
+
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// Workspace of one pass: disparities, then decoder input rows at rows_at.
+size_t query_workspace(int64_t pass, const MlpArgs& M, oo_dtype md, size_t& rows_at) {
+  rows_at = align256((size_t)pass * sizeof(float));
+  return rows_at + align256((size_t)pass * M.K0 * (md == OO_F32 ? 4 : 2));
+}
 
 struct Workspace {
   size_t Lq, lossp, seeds, nidx, uv, pos, dh, wt[OO_MAX_LAYERS], dwp, order, rank, scount, stotal, sstart, gpad, total;
@@ -574,23 +609,62 @@ int oo_query_fwd(const oo_tree* tree, const oo_mlp* mlp, const float* x, const f
   g_err[0] = 0;
   TreeArgs T;
   MlpArgs M;
+  DispArgs G;
+  int rc = check_query(tree, mlp, x, dir, attr, B, rgb_out, T, M, G);
+  if (rc || B == 0) return rc;
+  ProfScope ps(OO_PROF_QUERY, stream);
+  const QueryOut O{nullptr, nullptr, nullptr, nullptr, 0};
+  return hip_status(launch_query(T, tree->feat_dtype, M, mlp->dtype, query_src(x, dir, attr, 0, B, M), B, rgb_out, O, G,
+                                 stream),
+                    "query_fwd launch");
+}
+
+int oo_query_workspace_bytes(const oo_tree* tree, const oo_mlp* mlp, int64_t B, size_t* bytes) {
+  g_err[0] = 0;
+  TreeArgs T;
+  MlpArgs M;
+  DispArgs G;
   int rc = check_tree(tree, T);
   if (rc) return rc;
   if ((rc = check_mlp(mlp, tree->n_levels * tree->C, M))) return rc;
   if ((rc = check_pair(tree, mlp))) return rc;
-  DispArgs G;
   if ((rc = check_disparity(tree, G, false))) return rc;
   if (B < 0) return fail(OO_EINVAL, "B must be >= 0");
-  if (B == 0) return OO_OK;
-  if (!x || !dir || !rgb_out) return fail(OO_EINVAL, "x, dir and rgb_out are required");
-  if (M.E > 0 && !attr) return fail(OO_EINVAL, "attr is required: the decoder reads %d surface attributes", M.E);
-  QuerySrc src{x, dir, B, x, dir};
-  src.gA = src.gB = attr;
-  src.E = M.E;
+  if (!bytes) return fail(OO_EINVAL, "bytes is NULL");
+  size_t rows_at;
+  *bytes = G.n_levels ? query_workspace(query_pass(B), M, mlp->dtype, rows_at) : 0;
+  return OO_OK;
+}
+
+int oo_query_fwd_ws(const oo_tree* tree, const oo_mlp* mlp, const float* x, const float* dir, const float* attr,
+                    int64_t B, float* rgb_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+  g_err[0] = 0;
+  TreeArgs T;
+  MlpArgs M;
+  DispArgs G;
+  int rc = check_query(tree, mlp, x, dir, attr, B, rgb_out, T, M, G);
+  if (rc || B == 0) return rc;
+  if (!G.n_levels) return oo_query_fwd(tree, mlp, x, dir, attr, B, rgb_out, stream);
+  const int64_t pass = query_pass(B);
+  size_t rows_at;
+  const size_t need = query_workspace(pass, M, mlp->dtype, rows_at);
+  if (!workspace || workspace_bytes < need)
+    return fail(OO_EINVAL, "workspace of %zu bytes is smaller than the %zu this problem needs",
+                workspace ? workspace_bytes : 0, need);
+  float* const disp = static_cast<float*>(workspace);
+  void* const rows = static_cast<char*>(workspace) + rows_at;
   ProfScope ps(OO_PROF_QUERY, stream);
-  const QueryOut O{nullptr, nullptr, nullptr, nullptr, 0};
-  return hip_status(launch_query(T, tree->feat_dtype, M, mlp->dtype, src, B, rgb_out, O, G, stream),
-                    "query_fwd launch");
+  for (int64_t q0 = 0; q0 < B; q0 += pass) {
+    const int64_t n = std::min(pass, B - q0);
+    const QuerySrc src = query_src(x, dir, attr, q0, n, M);
+    QueryOut O{nullptr, nullptr, nullptr, nullptr, 0};
+    O.disp = disp;
+    hipError_t e = launch_predict(G, src, n, disp, 1, stream);
+    if (e == hipSuccess) e = launch_encode_rows(T, tree->feat_dtype, M, src, n, rows, O, stream);
+    if (e == hipSuccess) e = launch_mlp(M, mlp->dtype, rows, n, rgb_out + 3 * q0, stream);
+    if (e != hipSuccess) return hip_status(e, "query_fwd launch");
+  }
+  return OO_OK;
 }
 
 int oo_residual_workspace_bytes(const oo_tree* tree, const oo_mlp* mlp, const oo_residual_batch* batch, size_t* bytes) {

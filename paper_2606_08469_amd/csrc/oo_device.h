@@ -142,6 +142,23 @@ __device__ __forceinline__ uint32_t hash_entry(const DispArgs& G, int i, uint32_
   return (a ^ (b * 2654435761u) ^ (c * 805459861u)) & ((1u << G.log2_T) - 1u);
 }
 
+// The eight entries of the cell at `base` (corner d = dx | dy << 1 | dz << 2),
+// as hash_entry gives them: the level's indexing is decided once, and the
+// products are shared between the corners.
+__device__ __forceinline__ void hash_entries8(const DispArgs& G, int i, const int base[3], uint32_t e[8]) {
+  const uint32_t a = base[0], b = base[1], c = base[2];
+  if ((G.dense_mask >> i) & 1u) {
+    const uint32_t N1 = (uint32_t)G.res[i] + 1u, e0 = a + N1 * (b + N1 * c), N2 = N1 * N1;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) e[d] = e0 + (d & 1) + ((d & 2) ? N1 : 0u) + ((d & 4) ? N2 : 0u);
+  } else {
+    const uint32_t hb = b * 2654435761u, hc = c * 805459861u, mask = (1u << G.log2_T) - 1u;
+    const uint32_t hb1 = hb + 2654435761u, hc1 = hc + 805459861u;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) e[d] = ((a + (d & 1)) ^ ((d & 2) ? hb1 : hb) ^ ((d & 4) ? hc1 : hc)) & mask;
+  }
+}
+
 // The predictor's input [encoding, unit(w_r), 0] (zeros past it).
 __device__ __forceinline__ void disparity_input(const DispArgs& G, const float x[3], const float u[3], float (&a)[kDispK]) {
 #pragma unroll
@@ -155,10 +172,11 @@ __device__ __forceinline__ void disparity_input(const DispArgs& G, const float x
 #pragma unroll
       for (int ax = 0; ax < 3; ++ax) hash_cell(x[ax], N, base[ax], f[ax]);
       const float2* tab = reinterpret_cast<const float2*>(G.tables) + ((size_t)i << G.log2_T);
+      uint32_t en[8];
+      hash_entries8(G, i, base, en);
       float2 r[8];
 #pragma unroll
-      for (int d = 0; d < 8; ++d)
-        r[d] = tab[hash_entry(G, i, base[0] + (d & 1), base[1] + ((d >> 1) & 1), base[2] + (d >> 2))];
+      for (int d = 0; d < 8; ++d) r[d] = tab[en[d]];
       float e0 = 0.0f, e1 = 0.0f;
 #pragma unroll
       for (int d = 0; d < 8; ++d) {
@@ -237,32 +255,6 @@ __device__ __forceinline__ void disp_hidden2(const DispArgs& G, const float* W0,
       if ((o & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
   }
-}
-
-// Predicted disparity d(x, w_r) of one lane's query (u = unit(w_r)).
-__device__ __forceinline__ float predict_disparity(const DispArgs& G, const float x[3], const float u[3]) {
-  float a[kDispK];
-  disparity_input(G, x, u, a);
-  // (selected, not indexed: a runtime index into the argument's arrays
-  // would copy them to scratch memory)
-  const bool two = G.n_layers == 3;
-  const float* Wo = two ? G.W[2] : G.W[1];
-  float d = (two ? G.b[2] : G.b[1])[0];
-  if (two) {
-    float z2[kDispH];
-    disp_hidden2(G, G.W[0], G.W[1], a, z2, [](int, const float (&)[kDispChunk]) {});
-#pragma unroll
-    for (int o = 0; o < kDispH; ++o) d += Wo[o] * fmaxf(z2[o], 0.0f);
-  } else {
-#pragma unroll 1
-    for (int c = 0; c < kDispH; c += kDispChunk) {
-      float h1[kDispChunk];
-      disp_chunk0(G, G.W[0], c, a, h1);
-#pragma unroll
-      for (int j = 0; j < kDispChunk; ++j) d += Wo[c + j] * h1[j];
-    }
-  }
-  return d;
 }
 
 // Unit vector of a direction (zero stays zero).

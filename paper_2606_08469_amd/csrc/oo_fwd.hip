@@ -12,12 +12,12 @@ namespace oo {
 // Standalone encoding: one thread per query, h written row-major to memory.
 // ---------------------------------------------------------------------------
 // MODE: 0 node + bilinear, 1 the paper's scheme, 2 the paper's scheme with
-// the disparity shift (predicted per query from G).
+// the disparity shift (FP32 features; the first entry of each row holds the
+// query's disparity when the kernel starts, see launch_predict).
 template <class TT, class HT, int C, int MODE>
 __global__ __launch_bounds__(256) void encode_kernel(const TreeArgs T, const float* __restrict__ x,
                                                      const float* __restrict__ dir, int64_t B,
-                                                     HT* __restrict__ h_out, int32_t* __restrict__ idx_out,
-                                                     const DispArgs G) {
+                                                     HT* __restrict__ h_out, int32_t* __restrict__ idx_out) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool valid = q < B;
   float xq[3] = {0.f, 0.f, 0.f}, dq[3] = {0.f, 0.f, 1.f};
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const TreeArgs T, const flo
     float u[3] = {0.f, 0.f, 0.f}, disp = 0.0f;
     if constexpr (MODE == 2) {
       unit_dir3(dq, u);
-      disp = predict_disparity(G, xq, u);
+      if (valid) disp = to_f32(h_out[q * (int64_t)(T.L * C)]);
     }
     const int L = T.L;
     HT* hrow = h_out + (valid ? q : 0) * (int64_t)(L * C);
@@ -89,12 +89,12 @@ __global__ __launch_bounds__(256) void encode_kernel(const TreeArgs T, const flo
 // In the paper's scheme the stored indices are the eight corner cells'
 // nodes per level ([L][8][n_idx]) and the query's position is kept too
 // (pos_out, [n_idx]); the backward recomputes the trilinear weights from it.
-// MODE as for encode_kernel; with the shift the query's disparity goes to
-// pos_out's w and its unit lookup direction to wdir_out.
+// MODE as for encode_kernel; with the shift rgb[3 q] holds query q's
+// disparity when the kernel starts (the wave that reads it writes the
+// radiance there).
 template <class TT, class MT, int C, int H, bool WLDS, int MODE>
 __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpArgs M, const QuerySrc src,
-                                                    int64_t Q, float* __restrict__ rgb, const QueryOut O,
-                                                    const DispArgs G) {
+                                                    int64_t Q, float* __restrict__ rgb, const QueryOut O) {
   int32_t* __restrict__ idx_out = O.idx;
   float2* __restrict__ uv_out = O.uv;
   float4* __restrict__ pos_out = O.pos;
@@ -133,8 +133,7 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
       float u[3] = {0.f, 0.f, 0.f}, disp = 0.0f;
       if constexpr (MODE >= 2) {
         unit_dir3(d, u);
-        disp = predict_disparity(G, x, u);
-        if (keep) O.wdir[q] = make_float4(u[0], u[1], u[2], 0.0f);
+        if (valid) disp = rgb[3 * q];
       }
       if (keep) pos_out[q] = make_float4(x[0], x[1], x[2], disp);
       encode_paper<TT, C, MODE >= 2>(T, valid, x, s, t, [&](int l, const float (&h)[C], const int (&node)[8]) {
@@ -220,214 +219,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C == 4 ? 4 
 #pragma unroll
     for (int c = 0; c < 4; ++c) v[c] = from_f32<MT>(g4[c]);
     *reinterpret_cast<v4*>(row + K0 - E + k) = v;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Disparity predictor on the matrix cores: each wave encodes 64 queries'
-// positions (hash grid) and lookup directions into its FP32 activation tile
-// and runs the predictor's MLP on it like the decoder's, writing d per
-// query. FP32 path: 16x16x4 FP32 MFMA, weights from L2. 16-bit path
-// (SPLIT): every operand is split into two BF16 parts, x = hi + lo with
-// hi = bf16(x) and lo = bf16(x - hi) (about 16 significant bits, FP32's
-// exponent range), and each product is hi hi + hi lo + lo hi on 16x16x32
-// BF16 MFMA with FP32 accumulation: three MFMAs of 16 cycles for each
-// eight FP32 ones of 32. The weights are split once per workgroup into LDS.
-// hi + lo holds x to 2^-16 relative (each part rounds to 8 significant
-// bits) and the dropped lo lo term is below 2^-16 of the product, so each
-// product carries at most about 3 * 2^-16 relative error. (A plain 16-bit
-// predictor moves shifted lookups across triangle edges often enough to
-// break its gradients' agreement.)
-// ---------------------------------------------------------------------------
-
-// Packs the predictor's FP32 weights into LDS in fragment order, split into
-// BF16 hi (at hi) and lo (at hi + the packed size) parts.
-__device__ inline void pack_weights_split(const MlpArgs& M, bf16* hi, int total_elems) {
-  pack_layers<float>(M, [&](int f, int lane, const f32x8& w) {
-    bf16x8 h, l;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      h[i] = from_f32<bf16>(w[i]);
-      l[i] = from_f32<bf16>(w[i] - to_f32(h[i]));
-    }
-    reinterpret_cast<bf16x8*>(hi)[f * kWave + lane] = h;
-    reinterpret_cast<bf16x8*>(hi + total_elems)[f * kWave + lane] = l;
-  });
-}
-
-__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& h, bf16x8& l) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const bf16 a = from_f32<bf16>(v[i]);
-    h[i] = a;
-    l[i] = from_f32<bf16>(v[i] - to_f32(a));
-  }
-}
-
-// acc += A B with A, B split: hi hi + hi lo + lo hi.
-__device__ __forceinline__ f32x4 mma_split(const bf16x8& ah, const bf16x8& al, const bf16x8& bh, const bf16x8& bl,
-                                           f32x4 c) {
-  c = mma(ah, bh, c);
-  c = mma(ah, bl, c);
-  return mma(al, bh, c);
-}
-
-// The predictor's MLP (width 64) on N-tiles t0 .. t0+NT-1 with split
-// operands; out[t] rows 0.. = d in lanes 0..15. The input's first K-chunk
-// (the 32 hash features) comes from the wave's one-chunk FP32 tile; the
-// second holds only the unit direction (inputs 32..34, input 35 zero),
-// which the lanes of group 0 take from the lane that owns the query, so the
-// tile needs half the LDS.
-static_assert(kDispK == 36, "the predictor's input is 32 hash features, the unit direction and a zero");
-template <int NT>
-__device__ inline void disp_mlp_split(const MlpArgs& M, const WFrag<bf16, true>& Wh, const WFrag<bf16, true>& Wl,
-                                      const float* bias, const float* htile, const float u[3], int t0, int lane,
-                                      f32x4 out[NT]) {
-  constexpr int MH = kDispH / 16, KH = kDispH / 32;
-  f32x4 acc[MH][NT];
-#pragma unroll
-  for (int m = 0; m < MH; ++m) {
-    const f32x4 bt = bias_tile(bias, m, lane);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[m][t] = bt;
-  }
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    bf16x8 bh[NT], bl[NT], ah[MH], al[MH];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      float v[8];
-      if (kb == 0) {
-        const f32x8 x = htile_get<float>(htile, 1, t0 + t, 0, lane);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = x[i];
-      } else {
-        // slot i < 4 of group g holds input 32 + 4g + i; the rest are >= 48
-        const int src = 16 * (t0 + t) + (lane & 15);
-        const float s0 = __shfl(u[0], src), s1 = __shfl(u[1], src), s2 = __shfl(u[2], src);
-        const bool g0 = (lane >> 4) == 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = 0.0f;
-        v[0] = g0 ? s0 : 0.0f;
-        v[1] = g0 ? s1 : 0.0f;
-        v[2] = g0 ? s2 : 0.0f;
-      }
-      split8(v, bh[t], bl[t]);
-    }
-#pragma unroll
-    for (int m = 0; m < MH; ++m) {
-      ah[m] = Wh.get(M, 0, m, kb, lane);
-      al[m] = Wl.get(M, 0, m, kb, lane);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int m = 0; m < MH; ++m)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[m][t] = mma_split(ah[m], al[m], bh[t], bl[t], acc[m][t]);
-  }
-  // ReLU'd outputs of tiles (2kb, 2kb+1) are the next layer's chunk kb
-  auto chain = [&](int kb, int t, bf16x8& h, bf16x8& l) {
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[j] = fmaxf(acc[2 * kb][t][j], 0.0f);
-      v[4 + j] = fmaxf(acc[2 * kb + 1][t][j], 0.0f);
-    }
-    split8(v, h, l);
-  };
-  for (int layer = 1; layer < M.n_layers - 1; ++layer) {
-    bf16x8 bh[KH][NT], bl[KH][NT];
-#pragma unroll
-    for (int kb = 0; kb < KH; ++kb)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) chain(kb, t, bh[kb][t], bl[kb][t]);
-#pragma unroll
-    for (int m = 0; m < MH; ++m) {
-      const f32x4 bt = bias_tile(bias + layer * kDispH, m, lane);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[m][t] = bt;
-    }
-#pragma unroll
-    for (int kb = 0; kb < KH; ++kb) {
-      bf16x8 ah[MH], al[MH];
-#pragma unroll
-      for (int m = 0; m < MH; ++m) {
-        ah[m] = Wh.get(M, layer, m, kb, lane);
-        al[m] = Wl.get(M, layer, m, kb, lane);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int m = 0; m < MH; ++m)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[m][t] = mma_split(ah[m], al[m], bh[kb][t], bl[kb][t], acc[m][t]);
-    }
-  }
-  const int lo = M.n_layers - 1;
-  const f32x4 bo = bias_tile(bias + lo * kDispH, 0, lane);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) out[t] = bo;
-#pragma unroll
-  for (int kb = 0; kb < KH; ++kb) {
-    const bf16x8 ah = Wh.get(M, lo, 0, kb, lane), al = Wl.get(M, lo, 0, kb, lane);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      bf16x8 bh, bl;
-      chain(kb, t, bh, bl);
-      out[t] = mma_split(ah, al, bh, bl, out[t]);
-    }
-  }
-}
-
-template <bool SPLIT>
-__global__ __launch_bounds__(256) void disparity_fwd_kernel(const DispArgs G, const MlpArgs P, const QuerySrc src,
-                                                            int64_t Q, float* __restrict__ d_out) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int NT = 2;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  const int KB0 = (P.K0 + 31) / 32;
-  const int KBT = SPLIT ? 1 : KB0;  // K-chunks the FP32 tile holds
-  const int wl_elems = SPLIT ? packed_weight_elems<bf16>(P.n_layers, P.K0, P.H) : 0;
-  float* const bias = reinterpret_cast<float*>(smem);
-  bf16* const wl = reinterpret_cast<bf16*>(bias + bias_floats(P.n_layers, kDispH));
-  float* const htile = reinterpret_cast<float*>(wl + 2 * wl_elems) + wave * (4 * KBT * kWave * 8);
-  load_biases_lds(P, bias);
-  if (SPLIT) pack_weights_split(P, wl, wl_elems);
-  {  // zero the K padding of this lane's row once
-    const float z[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k = P.K0; k < 32 * KBT; k += 4) htile_put4<float>(htile, KBT, lane, k, z);
-  }
-  __syncthreads();
-  const WFrag<float, false> W{nullptr, KB0};
-  const WFrag<bf16, true> Wh{wl, KB0}, Wlo{wl + wl_elems, KB0};
-  const int64_t n_tiles = (Q + 63) / 64;
-  const TileRange tr = xcd_tiles(n_tiles, waves, wave);
-  for (int64_t tile = tr.first; tile < tr.end; tile += tr.stride) {
-    const int64_t q = tile * 64 + lane;
-    float x[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 1.f}, u[3];
-    if (q < Q) load_query(src, q, x, d);
-    unit_dir3(d, u);
-    float a[kDispK];
-    disparity_input(G, x, u, a);
-#pragma unroll
-    for (int k = 0; k < (SPLIT ? 32 : kDispK); k += 4) htile_put4<float>(htile, KBT, lane, k, &a[k]);
-    wave_lds_sync();
-#pragma unroll
-    for (int t0 = 0; t0 < 4; t0 += NT) {
-      f32x4 out[NT];
-      if constexpr (SPLIT)
-        disp_mlp_split<NT>(P, Wh, Wlo, bias, htile, u, t0, lane, out);
-      else
-        mlp_forward_tiles<float, kDispH, NT, (kDispK + 31) / 32>(
-            P, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<float>(htile, KB0, t0 + t, kb, lane); }, out);
-      if (lane < 16) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int64_t qq = tile * 64 + 16 * (t0 + t) + lane;
-          if (qq < Q) d_out[qq] = out[t][0];
-        }
-      }
-    }
-    wave_lds_sync();
   }
 }
 
@@ -576,12 +367,14 @@ static hipError_t launch_encode_t(const TreeArgs& T, const float* x, const float
   const int64_t blocks = (B + 255) / 256;
   HT* hp = reinterpret_cast<HT*>(h);
   if (T.interp != OO_INTERP_PAPER)
-    hipLaunchKernelGGL((encode_kernel<TT, HT, C, 0>), dim3((unsigned)blocks), dim3(256), 0, st, T, x, d, B, hp, idx, G);
+    hipLaunchKernelGGL((encode_kernel<TT, HT, C, 0>), dim3((unsigned)blocks), dim3(256), 0, st, T, x, d, B, hp, idx);
   else if (G.n_levels == 0)
-    hipLaunchKernelGGL((encode_kernel<TT, HT, C, 1>), dim3((unsigned)blocks), dim3(256), 0, st, T, x, d, B, hp, idx, G);
-  else if constexpr (sizeof(HT) == 4)  // the shifted encoding writes FP32 features only
-    hipLaunchKernelGGL((encode_kernel<TT, HT, C, 2>), dim3((unsigned)blocks), dim3(256), 0, st, T, x, d, B, hp, idx, G);
-  else
+    hipLaunchKernelGGL((encode_kernel<TT, HT, C, 1>), dim3((unsigned)blocks), dim3(256), 0, st, T, x, d, B, hp, idx);
+  else if constexpr (sizeof(HT) == 4) {  // the shifted encoding writes FP32 features only
+    const hipError_t e = launch_predict(G, QuerySrc{x, d, B, x, d}, B, hp, (int64_t)T.L * C, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((encode_kernel<TT, HT, C, 2>), dim3((unsigned)blocks), dim3(256), 0, st, T, x, d, B, hp, idx);
+  } else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -607,18 +400,6 @@ hipError_t launch_encode(const TreeArgs& T, oo_dtype td, const float* x, const f
                     : launch_encode_h<f16, 8>(T, x, d, B, h, hd, idx, G, st);
   return T.C == 4 ? launch_encode_h<bf16, 4>(T, x, d, B, h, hd, idx, G, st)
                   : launch_encode_h<bf16, 8>(T, x, d, B, h, hd, idx, G, st);
-}
-
-// Grid of the tile kernels for a workgroup of `waves` waves using lds bytes.
-// One workgroup per tile up to the resident count, so that a small batch
-// spreads over the chip (xcd_tiles hands out the tiles to match).
-static int tile_grid(int64_t n_tiles, size_t lds) {
-  // LDS per CU on gfx950 is 160 KiB: one or two workgroups fit per CU.
-  const int per_cu = lds * 2 <= (size_t)160 * 1024 ? 2 : 1;
-  int64_t g = (int64_t)device_cus() * per_cu;
-  if (g > n_tiles) g = n_tiles;
-  if (g >= 8) g -= g % 8;
-  return (int)(g > 0 ? g : 1);
 }
 
 // The shape without weights in LDS: as many 64-query tiles as fit, up to 8.
@@ -657,7 +438,7 @@ static void tile_launch_shape(const MlpArgs& M, int64_t Q, bool& wlds, int& wave
 
 template <class TT, class MT, int C, int H, int MODE>
 static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
-                                 const QueryOut& O, const DispArgs& G, hipStream_t st) {
+                                 const QueryOut& O, hipStream_t st) {
   bool wlds;
   int waves, grid;
   size_t lds;
@@ -669,11 +450,11 @@ static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const Quer
   if (wlds) {
     auto k = query_kernel<TT, MT, C, H, true, MODE >= 2 ? 1 : MODE>;
     hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O, G);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O);
   } else {
     auto k = query_kernel<TT, MT, C, H, false, MODE>;
     hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O, G);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O);
   }
   return hipGetLastError();
 }
@@ -681,9 +462,11 @@ static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const Quer
 template <class TT, class MT, int C, int H>
 static hipError_t launch_query_t(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
                                  const QueryOut& O, const DispArgs& G, hipStream_t st) {
-  if (T.interp != OO_INTERP_PAPER) return launch_query_p<TT, MT, C, H, 0>(T, M, src, Q, rgb, O, G, st);
-  if (G.n_levels == 0) return launch_query_p<TT, MT, C, H, 1>(T, M, src, Q, rgb, O, G, st);
-  return launch_query_p<TT, MT, C, H, 2>(T, M, src, Q, rgb, O, G, st);
+  if (T.interp != OO_INTERP_PAPER) return launch_query_p<TT, MT, C, H, 0>(T, M, src, Q, rgb, O, st);
+  if (G.n_levels == 0) return launch_query_p<TT, MT, C, H, 1>(T, M, src, Q, rgb, O, st);
+  const hipError_t e = launch_predict(G, src, Q, rgb, 3, st);
+  if (e != hipSuccess) return e;
+  return launch_query_p<TT, MT, C, H, 2>(T, M, src, Q, rgb, O, st);
 }
 
 template <class TT, class MT, int C>
@@ -769,38 +552,6 @@ hipError_t launch_encode_rows(const TreeArgs& T, oo_dtype td, const MlpArgs& M, 
   else
     T.C == 4 ? launch_encode_rows_t<bf16, bf16, 4>(T, src, Q, M.K0, M.E, h_rows, O, st)
              : launch_encode_rows_t<bf16, bf16, 8>(T, src, Q, M.K0, M.E, h_rows, O, st);
-  return hipGetLastError();
-}
-
-hipError_t launch_disparity_fwd(const DispArgs& G, oo_dtype md, const QuerySrc& src, int64_t Q, float* d_out,
-                                hipStream_t st) {
-  if (Q == 0) return hipSuccess;
-  MlpArgs P{};
-  P.n_layers = G.n_layers;
-  P.K0 = kDispK;
-  P.E = 0;
-  P.H = kDispH;
-  P.n_out = 1;
-  for (int i = 0; i < kMaxLayers; ++i) {
-    P.W[i] = i < G.n_layers ? G.W[i] : nullptr;
-    P.b[i] = i < G.n_layers ? G.b[i] : nullptr;
-  }
-  // four-wave workgroups, two per CU: four 16 KiB FP32 tiles, or for the
-  // split variant the hi and lo weight copies (2 x 18 KiB) and four 8 KiB
-  // one-chunk tiles
-  const bool split = md != OO_F32;
-  constexpr int waves = 4;
-  const size_t wbytes = split ? (size_t)2 * packed_weight_elems<bf16>(P.n_layers, P.K0, P.H) * sizeof(bf16) : 0;
-  const int kbt = split ? 1 : (P.K0 + 31) / 32;
-  const size_t lds = bias_bytes(P) + wbytes + (size_t)waves * 4 * kbt * kWave * 8 * sizeof(float);
-  const int grid = tile_grid((Q + 63) / 64, lds);
-  if (split) {
-    hipFuncSetAttribute((const void*)disparity_fwd_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(disparity_fwd_kernel<true>, dim3(grid), dim3(64 * waves), lds, st, G, P, src, Q, d_out);
-  } else {
-    hipFuncSetAttribute((const void*)disparity_fwd_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(disparity_fwd_kernel<false>, dim3(grid), dim3(64 * waves), lds, st, G, P, src, Q, d_out);
-  }
   return hipGetLastError();
 }
 

@@ -59,9 +59,9 @@ hipError_t launch_mlp(const MlpArgs& M, oo_dtype md, const void* h, int64_t Q, f
 // [L][n_idx]; the paper's scheme: the eight corner nodes, [L][8][n_idx], and
 // the position, pos_out [n_idx]) and octahedral coordinates (uv_out,
 // [n_idx]).
-// With the disparity predictor (G.n_levels > 0; the paper's scheme only)
-// the fused kernel predicts each query's disparity, stores it in pos_out's
-// w and the unit lookup direction in wdir_out ([n_idx]).
+// With the disparity predictor (G.n_levels > 0; the paper's scheme only) the
+// shifted encode also keeps each query's disparity (pos_out's w) and unit
+// lookup direction (wdir_out, [n_idx]).
 struct QueryOut {
   int32_t* idx;
   float2* uv;
@@ -70,6 +70,10 @@ struct QueryOut {
   int64_t n_idx;
   const float* disp = nullptr;  // per-query disparity, read by the shifted encode into rows
 };
+// The predictor's d of Q queries into out[q * stride], in FP32 with every sum
+// in the order of its inputs.
+hipError_t launch_predict(const DispArgs& G, const QuerySrc& src, int64_t Q, float* out, int64_t stride,
+                          hipStream_t st);
 // The predictor's d for Q queries (matrix cores), into d_out [Q]: FP32 for
 // an FP32 model, split BF16 operands (hi + lo) for a 16-bit one.
 hipError_t launch_disparity_fwd(const DispArgs& G, oo_dtype md, const QuerySrc& src, int64_t Q, float* d_out,

@@ -218,6 +218,18 @@ __device__ inline void store_rgb(const f32x4 out[NT], int64_t q0, int64_t Q, int
   }
 }
 
+// Grid of the tile kernels for a workgroup using lds bytes: one workgroup
+// per tile up to the resident count, so that a small batch spreads over the
+// chip (xcd_tiles hands out the tiles to match).
+inline int tile_grid(int64_t n_tiles, size_t lds) {
+  // LDS per CU on gfx950 is 160 KiB: one or two workgroups fit per CU.
+  const int per_cu = lds * 2 <= (size_t)160 * 1024 ? 2 : 1;
+  int64_t g = (int64_t)device_cus() * per_cu;
+  if (g > n_tiles) g = n_tiles;
+  if (g >= 8) g -= g % 8;
+  return (int)(g > 0 ? g : 1);
+}
+
 inline size_t bias_bytes(const MlpArgs& M) { return (size_t)bias_floats(M.n_layers, M.H) * sizeof(float); }
 
 }  // namespace oo

@@ -1,13 +1,15 @@
 """Kernel variants and dispatch branches at the sizes where they can go
 wrong, against the FP64 oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from paper_2606_08469_amd import binding
+from paper_2606_08469_amd import binding, synth
 
-from _gpu import report, to_np
+from _gpu import rel_l2, report, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +50,72 @@ def test_decoder_shapes(widths, dtype, B, off):
     worst = float(np.max(np.abs(rgb[rows] - want) / (np.abs(want) + rms)))
     report(f"decoder {widths} {dtype} B={B}", worst=worst)
     assert worst <= (1e-5 if dtype == torch.float32 else 0.02)
+
+
+def small_paper_model(dtype, widths):
+    """Four levels of vertex maps over a random tree, with a predictor of one
+    or two hidden layers and a decoder that reads 4 attributes."""
+    g = np.random.default_rng(11)
+    s = (g.uniform(0, 1, (4000, 3)) ** 1.5).astype(np.float32)
+    nodes, lo = binding.build_octree(s, 3, 8)
+    res, C = [8, 8, 4, 2], 4
+    feat = [g.normal(0, 0.1, (int(n), r + 1, r + 1, C)).astype(np.float32) for n, r in zip(np.diff(lo), res)]
+    W, b = [], []
+    for i, o in ((20, 64), (64, 64), (64, 3)):
+        W.append((g.uniform(-1, 1, (o, i)) * np.sqrt(6.0 / (i + o))).astype(np.float32))
+        b.append((0.1 * g.normal(size=o)).astype(np.float32))
+    cfg = synth.CONFIGS[6]
+    disp = synth.init_disparity(cfg, log2_T=10, table_scale=0.5, d0=1.5, widths=widths)
+    for v in disp["b"][:-1]:
+        v[:] = 0.1 * g.normal(size=v.shape)
+    model = binding.OctaOctree(nodes, lo, res, C, feat, W, b, dtype=dtype, interp=binding.INTERP_PAPER, disparity=disp)
+    od = oracle.Disparity(disp["res"], synth.HASH_F, disp["log2_T"], disp["tables"], disp["W"], disp["b"])
+    return model, oracle.Tree(nodes, lo, res, C, feat, interp=binding.INTERP_PAPER, disp=od), oracle.MLP(W, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("widths", [(64,), (64, 64)])
+@pytest.mark.parametrize("B", [1, 63, 65, 1000, (1 << 20) + 65])
+def test_shifted_query_routes(dtype, widths, B):
+    """The shifted query with a workspace (three kernels, two passes above
+    2^20 queries), without one (predictor, then the fused kernel) and the
+    encode + decode pair: the first two agree bit for bit, and all with the
+    oracle at the bars of the shifted query (1e-5 in FP32, 1e-2 in FP16)."""
+    model, otree, omlp = small_paper_model(dtype, widths)
+    g = np.random.default_rng(B)
+    x = torch.from_numpy(g.uniform(-0.02, 1.02, (B, 3)).astype(np.float32)).cuda()
+    d = torch.from_numpy(g.normal(size=(B, 3)).astype(np.float32)).cuda()
+    attr = torch.from_numpy(g.normal(size=(B, 4)).astype(np.float32)).cuda()
+    print(f"[case] shifted query {dtype} {widths} B={B}", flush=True)
+    split = model(x, d, attr)
+    fused = torch.full((B, 3), 7.0, device="cuda")
+    ts, ms = model.tree.struct(model.work_feat), model.mlp.struct(model.work_W)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert binding.lib().oo_query_fwd(ctypes.byref(ts), ctypes.byref(ms), p(x), p(d), p(attr), B, p(fused),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert torch.equal(split, fused)
+    rows = np.unique(np.concatenate([np.arange(min(B, 200)), np.arange(max(0, B - 200), B)]))
+    want = oracle.query_fwd(otree, omlp, x.cpu().numpy()[rows], d.cpu().numpy()[rows], attr=attr.cpu().numpy()[rows])
+    err = rel_l2(to_np(split)[rows], want)
+    h, _ = binding.encode_query(model.tree, x, d, with_idx=False, feat=model.work_feat)
+    oh = oracle.encode(otree, x.cpu().numpy()[rows], d.cpu().numpy()[rows])[0]
+    herr = rel_l2(to_np(h)[rows], oh)
+    report(f"shifted query {dtype} {widths} B={B}", rgb=err, h=herr)
+    tol = 1e-5 if dtype == torch.float32 else 1e-2
+    assert err <= tol and herr <= tol
+
+
+def test_shifted_query_refuses_short_workspace():
+    model, _, _ = small_paper_model(torch.float32, (64,))
+    x = torch.rand(100, 3, device="cuda")
+    attr, rgb = torch.rand(100, 4, device="cuda"), torch.full((100, 3), 7.0, device="cuda")
+    ts, ms = model.tree.struct(), model.mlp.struct()
+    n = ctypes.c_size_t(0)
+    L = binding.lib()
+    assert L.oo_query_workspace_bytes(ctypes.byref(ts), ctypes.byref(ms), 100, ctypes.byref(n)) == 0 and n.value > 0
+    ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    for w, size in ((p(ws), n.value - 1), (None, n.value)):
+        assert L.oo_query_fwd_ws(ctypes.byref(ts), ctypes.byref(ms), p(x), p(x), p(attr), 100, p(rgb), w, size, None) == -1
+    torch.cuda.synchronize()
+    assert torch.all(rgb == 7.0)
