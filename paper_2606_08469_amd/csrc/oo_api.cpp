@@ -308,6 +308,7 @@ size_t query_workspace(int64_t pass, const MlpArgs& M, oo_dtype md, size_t& rows
 
 struct Workspace {
   size_t Lq, lossp, seeds, nidx, uv, pos, dh, wt[OO_MAX_LAYERS], dwp, order, rank, scount, stotal, sstart, gpad, total;
+  size_t brows;  // 16-bit decoders: the inputs of every backward query's decoder, [K0 / 4][Qb][4]
   size_t wdir, dd, gdwp, dsp, drows, hrows;  // the disparity predictor's: lookup directions, dLoss/d
                                              // disparity, parameter partials, disparity of every query,
                                              // backward rows, decoder input rows
@@ -370,6 +371,8 @@ Workspace workspace_layout(const MlpArgs& M, oo_dtype md, const oo_residual_batc
   o = align256(o + (size_t)Qb * sizeof(float2));
   w.pos = o;  // paper's scheme: position of every backward query, [Qb]
   o = align256(o + (paper ? (size_t)Qb * sizeof(float4) : 0));
+  w.brows = o;
+  o = align256(o + (runs_bwd16(M, md) ? (size_t)Qb * M.K0 * 2 : 0));
   w.dh = o;  // dLoss/dh of every backward query, [Qb][L C] FP32
   o = align256(o + (size_t)Qb * L * tree->C * sizeof(float));
   // with the disparity predictor: unit lookup direction [Qb] float4 and
@@ -614,8 +617,7 @@ int oo_query_fwd(const oo_tree* tree, const oo_mlp* mlp, const float* x, const f
   if (rc || B == 0) return rc;
   ProfScope ps(OO_PROF_QUERY, stream);
   const QueryOut O{nullptr, nullptr, nullptr, nullptr, 0};
-  return hip_status(launch_query(T, tree->feat_dtype, M, mlp->dtype, query_src(x, dir, attr, 0, B, M), B, rgb_out, O, G,
-                                 stream),
+  return hip_status(launch_query(T, mlp->dtype, M, query_src(x, dir, attr, 0, B, M), B, rgb_out, O, G, stream),
                     "query_fwd launch");
 }
 
@@ -734,6 +736,7 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
     ProfScope ps(OO_PROF_QUERY, stream);
     QueryOut O{nidx, reinterpret_cast<float2*>(ws + w.uv), reinterpret_cast<float4*>(ws + w.pos),
                G.n_levels ? reinterpret_cast<float4*>(ws + w.wdir) : nullptr, w.Qb};
+    if (runs_bwd16(M, mlp->dtype)) O.rows = ws + w.brows;
     if (G.n_levels) {
       // every query's disparity on the matrix cores, the shifted encode into
       // decoder input rows, then the decoder over the rows
@@ -746,7 +749,7 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
       if (e != hipSuccess) return hip_status(e, "shifted encode launch");
       e = launch_mlp(M, mlp->dtype, hrows, Q, Lq, stream);
     } else {
-      e = launch_query(T, tree->feat_dtype, M, mlp->dtype, sorted, Q, Lq, O, G, stream);
+      e = launch_query(T, mlp->dtype, M, sorted, Q, Lq, O, G, stream);
     }
   }
   if (e != hipSuccess) return hip_status(e, "residual query launch");
@@ -798,23 +801,23 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
   const bool full = batch->grad_through_rhs && !batch->target_override && batch->N > 0;
   const int64_t Qb = full ? A.B * (1 + A.N) : A.B;
   const float post_scale = (float)(1.0 / (3.0 * (double)A.B));
-  hipError_t e;
-  {
-    ProfScope ps(OO_PROF_SEEDS, stream);
-    e = launch_seeds(A, resid, rhs, grad_loss, full ? 1 : 0, seeds, stream);
-    if (e == hipSuccess) e = launch_fill_zero(gpad, w.pad_total, stream);
-    if (e == hipSuccess && G.n_levels) e = launch_fill_zero(reinterpret_cast<float*>(ws + w.dd), Qb, stream);
-  }
-  if (e != hipSuccess) return hip_status(e, "seed launch");
-  {
-    ProfScope ps(OO_PROF_TRANSPOSE, stream);
-    e = launch_transpose_weights(M, mlp->dtype, Wt, stream);
-  }
-  if (e != hipSuccess) return hip_status(e, "transpose launch");
   // the forward's bucketed order: its first Qb sorted positions are the
   // backward's queries (all LHS queries come first); node indices and
   // octahedral coordinates were stored at those positions
   const int32_t* order = reinterpret_cast<const int32_t*>(ws + w.order);
+  hipError_t e;
+  {
+    ProfScope ps(OO_PROF_SEEDS, stream);
+    e = launch_seeds(A, resid, rhs, grad_loss, order, Qb, seeds, stream);
+    if (e == hipSuccess) e = launch_fill_zero(gpad, w.pad_total, stream);
+    if (e == hipSuccess && G.n_levels) e = launch_fill_zero(reinterpret_cast<float*>(ws + w.dd), Qb, stream);
+  }
+  if (e != hipSuccess) return hip_status(e, "seed launch");
+  if (!runs_bwd16(M, mlp->dtype)) {
+    ProfScope ps(OO_PROF_TRANSPOSE, stream);
+    e = launch_transpose_weights(M, mlp->dtype, Wt, stream);
+  }
+  if (e != hipSuccess) return hip_status(e, "transpose launch");
   const float2* uv = reinterpret_cast<const float2*>(ws + w.uv);
   const float4* pos = reinterpret_cast<const float4*>(ws + w.pos);
   float* dh = reinterpret_cast<float*>(ws + w.dh);
@@ -828,7 +831,8 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
       const int64_t q0 = c * chunk, qn = std::min(Qb - q0, chunk);
       if (qn <= 0) break;
       const int64_t LC = (int64_t)tree->n_levels * tree->C;
-      BwdArgs B{qn, nidx + q0, Qb, uv + q0, pos + q0, seeds, order + q0, Qb, partials, dh + q0 * LC, c > 0};
+      BwdArgs B{qn, nidx + q0, Qb, uv + q0, pos + q0, seeds + 3 * q0, order + q0, partials, dh + q0 * LC, c > 0};
+      B.rows = ws + w.brows + (size_t)q0 * 4 * 2;
       B.gA = batch->attr;
       B.gB = A.N > 0 ? batch->attr2 : batch->attr;
       B.nA = A.B;

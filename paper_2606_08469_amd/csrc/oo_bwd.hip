@@ -23,8 +23,7 @@
 
 #include <mutex>
 
-#include "oo_device.h"
-#include "oo_internal.h"
+#include "oo_bwd16.h"
 
 namespace oo {
 
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(64 * bwd_waves<MT>()) void bwd_kernel(const TreeArg
                                                              const BwdArgs A, const ParamLayout PL) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   typedef typename FragT<MT>::type frag;
-  const int64_t Q = A.Q, ldn = A.ldn, n_seed = A.n_seed;
+  const int64_t Q = A.Q, ldn = A.ldn;
   const int32_t* __restrict__ nidx = A.nidx;
   const float2* __restrict__ uv = A.uv;
   const float* __restrict__ seeds = A.seeds;
@@ -340,10 +339,10 @@ __global__ __launch_bounds__(64 * bwd_waves<MT>()) void bwd_kernel(const TreeArg
             if (A.shift) {  // each corner's cell along its shifted direction
               const float4 w4 = q < Q ? A.wdir[q] : make_float4(0.f, 0.f, 0.f, 0.f);
               const float u[3] = {w4.x, w4.y, w4.z};
-              gather_paper_level_shift<TT, C>(T, l, node, wc, xq, base, xp.w, u, h);
+              gather_paper_level_shift<TT, C>(T, l, node, wc, xq, base, xp.w, u).finish(h);
             } else {
               bary(s, t, T.res[l], slot, wv);
-              gather_paper_level<TT, C>(T, l, node, wc, slot, wv, h);
+              gather_paper_level<TT, C>(T, l, node, wc, slot, wv).finish(h);
             }
 #pragma unroll
             for (int c = 0; c < C; ++c) act0[tq_index(l * C + c, ql)] = from_f32<MT>(h[c]);
@@ -453,17 +452,11 @@ __global__ __launch_bounds__(64 * bwd_waves<MT>()) void bwd_kernel(const TreeArg
     // ---- 3. backward ------------------------------------------------------
     if (mh == 0) {  // seeds of the output layer into the seed buffer, rows 0..15
       const int64_t q = qbase + col;
-      // seeds are stored in the caller's query order
-      int64_t qs = q < Q ? q : -1;
-      if (order && qs >= 0) {
-        qs = order[q];
-        if (qs >= n_seed) qs = -1;
-      }
       f32x4 so[1];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int row = 4 * g + j;
-        so[0][j] = (row < 3 && qs >= 0) ? seeds[3 * qs + row] : 0.0f;
+        so[0][j] = (row < 3 && q < Q) ? seeds[3 * q + row] : 0.0f;
       }
       store_tq<MT, 1>(seedb, so, 0, 1, 3, nt, lane, false);
     }
@@ -606,42 +599,47 @@ __global__ __launch_bounds__(64 * bwd_waves<MT>()) void bwd_kernel(const TreeArg
   }
 }
 
-// Seeds of the backward: LHS point b gets 2 r_b grad_loss (divided by the
-// squared detached normaliser for the relative loss); with the gradient
-// through the target, secondary query (b, k) gets -seed_b * w_bk / N. The
-// 1 / (3B) mean factor is applied later in FP32, so that 16-bit matrix-core
-// operands stay far from underflow.
+// Seeds of the backward, in sorted order: LHS point b gets 2 r_b grad_loss
+// (divided by the squared detached normaliser for the relative loss); with
+// the gradient through the target, secondary query (b, k) gets
+// -seed_b * w_bk / N. The 1 / (3B) mean factor is applied later in FP32, so
+// that 16-bit matrix-core operands stay far from underflow. A source query
+// outside the batch (a workspace the forward did not fill) gets no seed.
 __device__ inline void bsdf_weight_b(const ResidualArgs& A, int64_t b, int k, float w[3]);
 
 __global__ __launch_bounds__(256) void seed_kernel(const ResidualArgs A, const float* __restrict__ resid,
                                                    const float* __restrict__ rhs, const double* __restrict__ grad_loss,
-                                                   int full, float* __restrict__ seeds) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= A.B) return;
+                                                   const int32_t* __restrict__ order, int64_t Qb,
+                                                   float* __restrict__ seeds) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= Qb) return;
   const float gam = (float)(*grad_loss);
-  float sd[3];
+  const int64_t q = order[p];
+  float sd[3] = {0.f, 0.f, 0.f};
+  if (q >= 0 && q < Qb) {
+    const bool lhs = q < A.B;
+    const int64_t b = lhs ? q : (q - A.B) / A.N;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const float r = resid[3 * b + c];
-    float v = 2.0f * r * gam;
-    if (A.loss_kind == 1) {
-      const float T = rhs[3 * b + c], Lh = r + T;
-      const float rho = fmaxf(Lh + T, 0.0f) + A.eps;
-      v /= rho * rho;
+    for (int c = 0; c < 3; ++c) {
+      const float r = resid[3 * b + c];
+      float v = 2.0f * r * gam;
+      if (A.loss_kind == 1) {
+        const float T = rhs[3 * b + c], Lh = r + T;
+        const float rho = fmaxf(Lh + T, 0.0f) + A.eps;
+        v /= rho * rho;
+      }
+      sd[c] = v;
     }
-    sd[c] = v;
-    seeds[3 * b + c] = v;
-  }
-  if (full && A.N > 0) {
-    const float invN = 1.0f / (float)A.N;
-    for (int k = 0; k < A.N; ++k) {
+    if (!lhs) {
+      const float invN = 1.0f / (float)A.N;
       float w[3];
-      bsdf_weight_b(A, b, k, w);
-      const int64_t q = A.B + b * A.N + k;
+      bsdf_weight_b(A, b, (int)(q - A.B - b * A.N), w);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) seeds[3 * q + c] = -sd[c] * w[c] * invN;
+      for (int c = 0; c < 3; ++c) sd[c] = -sd[c] * w[c] * invN;
     }
   }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) seeds[3 * p + c] = sd[c];
 }
 
 // Wt[i][o] = W[o][i], rows of Wt padded with zeros to ld = n_out rounded up
@@ -711,31 +709,36 @@ static size_t bwd_lds_total(int K0, int H, int n_layers, int L, int msz, bool& w
   return wl ? base + hwb : base;
 }
 
-size_t bwd_lds_bytes(const MlpArgs& M, oo_dtype md, int L) {
-  bool wl;
-  return bwd_lds_total(M.K0, M.H, M.n_layers, L, md == OO_F32 ? 4 : 2, wl);
-}
+// 16-bit decoders run the kernels of oo_bwd16.h where those have a workgroup
+// shape for them; the rest, and FP32, run bwd_kernel.
+bool runs_bwd16(const MlpArgs& M, oo_dtype md) { return md != OO_F32 && bwd16_shape(M).waves > 0; }
 
-// Persistent grid: as many workgroups as fit on the chip at once (LDS
-// bound, 160 KiB per CU on gfx950), so that there is one dW partial per
-// resident workgroup.
+// Persistent grid: as many workgroups as fit on the chip at once, so that
+// there is one dW partial per resident workgroup (LDS bound, 160 KiB per CU
+// on gfx950; the 16-bit kernels run one workgroup per CU).
 int bwd_grid(const MlpArgs& M, oo_dtype md, int L, int64_t Q) {
-  const int64_t n_tiles = (Q + kQW - 1) / kQW;
-  const size_t lds = bwd_lds_bytes(M, md, L);
-  int per_cu = (int)(kLdsBytes / (lds ? lds : 1));
-  const int by_waves = 16 / (md == OO_F32 ? bwd_waves<float>() : bwd_waves<f16>());  // at most 16 waves per CU
-  if (per_cu > by_waves) per_cu = by_waves;
-  per_cu = per_cu < 1 ? 1 : per_cu;
-  int64_t g = (int64_t)cu_count() * per_cu;
+  int64_t n_tiles, g = cu_count();
+  if (runs_bwd16(M, md)) {
+    const int rows = 16 * bwd16_shape(M).waves;
+    n_tiles = (Q + rows - 1) / rows;
+  } else {
+    n_tiles = (Q + kQW - 1) / kQW;
+    bool wl;
+    const size_t lds = bwd_lds_total(M.K0, M.H, M.n_layers, L, md == OO_F32 ? 4 : 2, wl);
+    int per_cu = (int)(kLdsBytes / lds);
+    const int by_waves = 16 / (md == OO_F32 ? bwd_waves<float>() : bwd_waves<f16>());  // at most 16 waves per CU
+    if (per_cu > by_waves) per_cu = by_waves;
+    g *= per_cu < 1 ? 1 : per_cu;
+  }
   if (g > n_tiles) g = n_tiles;
   return (int)(g > 0 ? g : 1);
 }
 
 hipError_t launch_seeds(const ResidualArgs& A, const float* resid, const float* rhs, const double* grad_loss,
-                        int full, float* seeds, hipStream_t st) {
-  if (A.B == 0) return hipSuccess;
-  hipLaunchKernelGGL(seed_kernel, dim3((unsigned)((A.B + 255) / 256)), dim3(256), 0, st, A, resid, rhs, grad_loss,
-                     full, seeds);
+                        const int32_t* order, int64_t Qb, float* seeds, hipStream_t st) {
+  if (Qb == 0) return hipSuccess;
+  hipLaunchKernelGGL(seed_kernel, dim3((unsigned)((Qb + 255) / 256)), dim3(256), 0, st, A, resid, rhs, grad_loss,
+                     order, Qb, seeds);
   return hipGetLastError();
 }
 
@@ -749,42 +752,50 @@ hipError_t launch_transpose_weights(const MlpArgs& M, oo_dtype md, void* const* 
   return hipGetLastError();
 }
 
-template <class TT, class MT, int C, int H>
-static hipError_t launch_bwd_t(const TreeArgs& T, const MlpArgs& M, const MlpArgs& Mt, const BwdArgs& A,
-                               const ParamLayout& PL, int grid, hipStream_t st) {
-  bool wl;
-  const size_t lds = bwd_lds_total(M.K0, H, M.n_layers, T.L, (int)sizeof(MT), wl);
-  const bool paper = T.interp == OO_INTERP_PAPER;
-  constexpr int NH = H == 128 ? 1 : 3;
-  auto k = wl ? (paper ? bwd_kernel<TT, MT, C, H, true, true, NH> : bwd_kernel<TT, MT, C, H, true, false, NH>)
-              : (paper ? bwd_kernel<TT, MT, C, H, false, true, NH> : bwd_kernel<TT, MT, C, H, false, false, NH>);
-  if (H == 128 && M.n_layers > 3)  // four hidden layers: their weights do not fit in LDS
-    k = paper ? bwd_kernel<TT, MT, C, H, false, true, 3> : bwd_kernel<TT, MT, C, H, false, false, 3>;
+template <class MT, int C, int H, bool WL, int NHH>
+static hipError_t launch_bwd_k(const TreeArgs& T, const MlpArgs& M, const MlpArgs& Mt, const BwdArgs& A,
+                               const ParamLayout& PL, int grid, size_t lds, hipStream_t st) {
+  auto k = T.interp == OO_INTERP_PAPER ? bwd_kernel<MT, MT, C, H, WL, true, NHH> : bwd_kernel<MT, MT, C, H, WL, false, NHH>;
   hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(k, dim3(grid), dim3(64 * bwd_waves<MT>()), lds, st, T, M, Mt, A, PL);
   return hipGetLastError();
 }
 
-template <class TT, class MT, int C>
-static hipError_t launch_bwd_c(const TreeArgs& T, const MlpArgs& M, const MlpArgs& Mt, const BwdArgs& A,
-                               const ParamLayout& PL, int grid, hipStream_t st) {
-  return M.H == 64 ? launch_bwd_t<TT, MT, C, 64>(T, M, Mt, A, PL, grid, st)
-                   : launch_bwd_t<TT, MT, C, 128>(T, M, Mt, A, PL, grid, st);
+template <int C>
+static hipError_t launch_bwd_f32(const TreeArgs& T, const MlpArgs& M, const MlpArgs& Mt, const BwdArgs& A,
+                                 const ParamLayout& PL, int grid, hipStream_t st) {
+  bool wl;
+  const size_t lds = bwd_lds_total(M.K0, M.H, M.n_layers, T.L, 4, wl);
+  if (M.H == 64)
+    return wl ? launch_bwd_k<float, C, 64, true, 3>(T, M, Mt, A, PL, grid, lds, st)
+              : launch_bwd_k<float, C, 64, false, 3>(T, M, Mt, A, PL, grid, lds, st);
+  if (M.n_layers > 3)  // three or four 128-wide hidden layers: their weights do not fit in LDS
+    return launch_bwd_k<float, C, 128, false, 3>(T, M, Mt, A, PL, grid, lds, st);
+  return wl ? launch_bwd_k<float, C, 128, true, 1>(T, M, Mt, A, PL, grid, lds, st)
+            : launch_bwd_k<float, C, 128, false, 1>(T, M, Mt, A, PL, grid, lds, st);
+}
+
+// The 16-bit decoders without a shape in oo_bwd16.h: four 128-wide hidden
+// layers with weights read from L2.
+template <class MT>
+static hipError_t launch_bwd_wide(const TreeArgs& T, const MlpArgs& M, const MlpArgs& Mt, const BwdArgs& A,
+                                  const ParamLayout& PL, int grid, hipStream_t st) {
+  bool wl;
+  const size_t lds = bwd_lds_total(M.K0, M.H, M.n_layers, T.L, sizeof(MT), wl);
+  return T.C == 4 ? launch_bwd_k<MT, 4, 128, false, 3>(T, M, Mt, A, PL, grid, lds, st)
+                  : launch_bwd_k<MT, 8, 128, false, 3>(T, M, Mt, A, PL, grid, lds, st);
 }
 
 hipError_t launch_bwd(const TreeArgs& T, oo_dtype td, const MlpArgs& M, oo_dtype md, void* const* Wt,
                       const BwdArgs& A, const ParamLayout& PL, int grid, hipStream_t st) {
   if (A.Q == 0) return hipSuccess;
+  if (runs_bwd16(M, md)) return launch_bwd16(M, md, T.L * T.C, A, PL, grid, st);
   MlpArgs Mt = M;
   for (int i = 0; i < M.n_layers; ++i) Mt.W[i] = Wt[i];
   if (td == OO_F32)
-    return T.C == 4 ? launch_bwd_c<float, float, 4>(T, M, Mt, A, PL, grid, st)
-                    : launch_bwd_c<float, float, 8>(T, M, Mt, A, PL, grid, st);
-  if (td == OO_F16)
-    return T.C == 4 ? launch_bwd_c<f16, f16, 4>(T, M, Mt, A, PL, grid, st) : launch_bwd_c<f16, f16, 8>(T, M, Mt, A, PL, grid, st);
-  return T.C == 4 ? launch_bwd_c<bf16, bf16, 4>(T, M, Mt, A, PL, grid, st)
-                  : launch_bwd_c<bf16, bf16, 8>(T, M, Mt, A, PL, grid, st);
-  (void)md;
+    return T.C == 4 ? launch_bwd_f32<4>(T, M, Mt, A, PL, grid, st) : launch_bwd_f32<8>(T, M, Mt, A, PL, grid, st);
+  if (td == OO_F16) return launch_bwd_wide<f16>(T, M, Mt, A, PL, grid, st);
+  return launch_bwd_wide<bf16>(T, M, Mt, A, PL, grid, st);
 }
 
 // Feature-gradient scatter: one lane per (query, tap, channel), level by

@@ -440,6 +440,53 @@ struct Texel<f16, C> : Texel16<f16, C> {};
 template <int C>
 struct Texel<bf16, C> : Texel16<bf16, C> {};
 
+// h + w r, four channels, rounded to 16 bits: FP16 in one rounding of the
+// exact sum (v_fma_mixlo/mixhi), BF16 by way of FP32.
+__device__ __forceinline__ f16x4 fma_round4(float w, const f16x4& r, const float* h) {
+  union {
+    f16x4 v;
+    uint32_t u[2];
+  } in, out;
+  in.v = r;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    uint32_t d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,1,0]" : "=v"(d) : "v"(w), "v"(in.u[p]), "v"(h[2 * p]));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
+        : "+v"(d)
+        : "v"(w), "v"(in.u[p]), "v"(h[2 * p + 1]));
+    out.u[p] = d;
+  }
+  return out.v;
+}
+__device__ __forceinline__ bf16x4 fma_round4(float w, const bf16x4& r, const float* h) {
+  bf16x4 x;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) x[c] = (bf16)(h[c] + w * (float)r[c]);
+  return x;
+}
+
+// A level feature before its last product: h + w r. finish() is the FP32
+// feature; round4(c) gives channels c .. c + 3 of a 16-bit table's feature
+// rounded once, the inputs that the backward recomputes the decoder from.
+template <class TT, int C>
+struct LastTerm {
+  float h[C], w;
+  typename Texel<TT, C>::raw r;
+  __device__ __forceinline__ void finish(float* out) const {
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[c] = h[c];
+    Texel<TT, C>::acc(r, w, out);
+  }
+  __device__ __forceinline__ auto round4(int c) const {
+    typedef TT v4 __attribute__((ext_vector_type(4)));
+    v4 x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = r[c + j];
+    return fma_round4(w, x, h + c);
+  }
+};
+
 // Per-level feature h_l of one query: the 4 taps of the level-l map of node
 // idx (zeros when idx < 0). Loads are issued branch-free (a missing level
 // reads texel 0 of the level table with weight 0).
@@ -502,9 +549,10 @@ __device__ inline void gather_levels(const TreeArgs& T, int l0, const int* idx, 
 // level l the lane first loads the node word that selects the level-(l+1)
 // node, then issues the 4 texel loads of level l, and only then consumes the
 // texels of level l-1; so while the dependent node-word chain advances, two
-// levels of gathers are in flight behind it. put(l, h, node) receives each
-// level's C features and node index (zeros and -1 where the tree has no
-// node). The wave stops walking once none of its lanes has a node left.
+// levels of gathers are in flight behind it. put(l, h, node, last) receives
+// each level's C features and node index (zeros and -1 where the tree has no
+// node), and the features before their last product. The wave stops walking
+// once none of its lanes has a node left.
 template <class TT, int C, class Put>
 __device__ inline void encode_pipelined(const TreeArgs& T, bool valid, const float x[3], float s, float t,
                                         Put&& put) {
@@ -515,6 +563,18 @@ __device__ inline void encode_pipelined(const TreeArgs& T, bool valid, const flo
   Raw rp[4];
   float wp[4] = {0.f, 0.f, 0.f, 0.f};
   int np = -1;  // node of the level whose texels are in flight
+  auto emit = [&](int lev) {
+    LastTerm<TT, C> t;
+#pragma unroll
+    for (int c = 0; c < C; ++c) t.h[c] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) Texel<TT, C>::acc(rp[k], wp[k], t.h);
+    t.w = wp[3];
+    t.r = rp[3];
+    float h[C];
+    t.finish(h);
+    put(lev, h, np, t);
+  };
   int l = 0;
   for (; l < L; ++l) {
     if (!__any(cur >= 0)) break;
@@ -538,14 +598,7 @@ __device__ inline void encode_pipelined(const TreeArgs& T, bool valid, const flo
       }
     }
     // 3. features of level l - 1
-    if (l > 0) {
-      float h[C];
-#pragma unroll
-      for (int c = 0; c < C; ++c) h[c] = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) Texel<TT, C>::acc(rp[k], wp[k], h);
-      put(l - 1, h, np);
-    }
+    if (l > 0) emit(l - 1);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       rp[k] = rn[k];
@@ -561,18 +614,9 @@ __device__ inline void encode_pipelined(const TreeArgs& T, bool valid, const flo
     }
   }
   // drain: the last level fetched, then zeros for levels never reached
-  if (l > 0) {
-    float h[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) h[c] = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) Texel<TT, C>::acc(rp[k], wp[k], h);
-    put(l - 1, h, np);
-  }
-  float z[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) z[c] = 0.0f;
-  for (; l < L; ++l) put(l, z, -1);
+  if (l > 0) emit(l - 1);
+  const LastTerm<TT, C> none{};
+  for (; l < L; ++l) put(l, none.h, -1, none);
 }
 
 // ---------------------------------------------------------------------------
@@ -771,15 +815,16 @@ __device__ __forceinline__ void shift_axes(const float x[3], int l, const int ba
 // corners at a time (12 entries of 16 bytes, or 6 of 32 bytes); corners
 // without a node read entry 0 of the level with weight 0.
 template <class TT, int C>
-__device__ inline void gather_paper_level(const TreeArgs& T, int l, const int node[8], const float wc[8],
-                                          const int slot[3], const float wv[3], float* h) {
+__device__ inline LastTerm<TT, C> gather_paper_level(const TreeArgs& T, int l, const int node[8], const float wc[8],
+                                                     const int slot[3], const float wv[3]) {
   typedef typename Texel<TT, C>::raw Raw;
   constexpr int CB = sizeof(TT) * C > 16 ? 2 : 4;  // corners per batch
+  LastTerm<TT, C> last;
   const int R = T.res[l];
   const int64_t E = (int64_t)(R + 1) * (R + 1);
   const TT* base = reinterpret_cast<const TT*>(T.feat[l]);
 #pragma unroll
-  for (int c = 0; c < C; ++c) h[c] = 0.0f;
+  for (int c = 0; c < C; ++c) last.h[c] = 0.0f;
 #pragma unroll
   for (int b0 = 0; b0 < 8; b0 += CB) {
     Raw r[CB][3];
@@ -794,19 +839,25 @@ __device__ inline void gather_paper_level(const TreeArgs& T, int l, const int no
 #pragma unroll
     for (int dd = 0; dd < CB; ++dd)
 #pragma unroll
-      for (int k = 0; k < 3; ++k) Texel<TT, C>::acc(r[dd][k], wc[b0 + dd] * wv[k], h);
+      for (int k = 0; k < 3; ++k) {
+        last.w = wc[b0 + dd] * wv[k];
+        last.r = r[dd][k];
+        if (b0 + dd < 7 || k < 2) Texel<TT, C>::acc(last.r, last.w, last.h);
+      }
   }
+  return last;
 }
 
 // The same level feature with the disparity shift: corner d's cell is read
 // at its own direction (x - centre) disp + u (one barycentric lookup per
 // corner).
 template <class TT, int C>
-__device__ __forceinline__ void gather_paper_level_shift(const TreeArgs& T, int l, const int node[8], const float wc[8],
-                                                const float x[3], const int base[3], float disp, const float u[3],
-                                                float* h) {
+__device__ __forceinline__ LastTerm<TT, C> gather_paper_level_shift(const TreeArgs& T, int l, const int node[8],
+                                                                    const float wc[8], const float x[3],
+                                                                    const int base[3], float disp, const float u[3]) {
   typedef typename Texel<TT, C>::raw Raw;
   constexpr int CB = sizeof(TT) * C > 16 ? 2 : 4;  // corners per batch
+  LastTerm<TT, C> last;
   const int R = T.res[l];
   const int64_t E = (int64_t)(R + 1) * (R + 1);
   const int64_t off = T.off[l];
@@ -814,7 +865,7 @@ __device__ __forceinline__ void gather_paper_level_shift(const TreeArgs& T, int 
   ShiftAxes A;
   shift_axes(x, l, base, disp, u, A);
 #pragma unroll
-  for (int c = 0; c < C; ++c) h[c] = 0.0f;
+  for (int c = 0; c < C; ++c) last.h[c] = 0.0f;
 #pragma unroll
   for (int b0 = 0; b0 < 8; b0 += CB) {
     Raw r[CB][3];
@@ -835,14 +886,20 @@ __device__ __forceinline__ void gather_paper_level_shift(const TreeArgs& T, int 
 #pragma unroll
     for (int dd = 0; dd < CB; ++dd)
 #pragma unroll
-      for (int k = 0; k < 3; ++k) Texel<TT, C>::acc(r[dd][k], wc[b0 + dd] * wv[dd][k], h);
+      for (int k = 0; k < 3; ++k) {
+        last.w = wc[b0 + dd] * wv[dd][k];
+        last.r = r[dd][k];
+        if (b0 + dd < 7 || k < 2) Texel<TT, C>::acc(last.r, last.w, last.h);
+      }
   }
+  return last;
 }
 
 // Encoding of one query in the paper's scheme, level by level: the eight
 // corners' nodes follow from the previous level's (their node words are
-// loaded while this level's entries are gathered). put(l, h, node) receives
-// each level's C features and the eight corner nodes. Once no lane of the
+// loaded while this level's entries are gathered). put(l, h, node, last)
+// receives each level's C features, the eight corner nodes and the features
+// before their last product. Once no lane of the
 // wave has a corner left, deeper levels are empty too (their cells' parents
 // are among this level's corners) and get zeros.
 // With SHIFT every corner's cell is read along its shifted direction
@@ -871,28 +928,28 @@ __device__ __forceinline__ void encode_paper(const TreeArgs& T, bool valid, cons
     for (int d = 0; d < 8; ++d) pword[d] = (l < D && node[d] >= 0) ? T.nodes[node[d]] : 0u;
     float wc[8];
     corner_weights(f, node, wc);
-    float h[C];
+    LastTerm<TT, C> last;
     if constexpr (SHIFT) {
-      gather_paper_level_shift<TT, C>(T, l, node, wc, x, base, disp, u, h);
+      last = gather_paper_level_shift<TT, C>(T, l, node, wc, x, base, disp, u);
     } else {
       float wv[3];
       int slot[3];
       bary(s, t, T.res[l], slot, wv);
-      gather_paper_level<TT, C>(T, l, node, wc, slot, wv, h);
+      last = gather_paper_level<TT, C>(T, l, node, wc, slot, wv);
     }
-    put(l, h, node);
+    float h[C];
+    last.finish(h);
+    put(l, h, node, last);
 #pragma unroll
     for (int a = 0; a < 3; ++a) pbase[a] = base[a];
 #pragma unroll
     for (int d = 0; d < 8; ++d) pnode[d] = node[d];
   }
-  float z[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) z[c] = 0.0f;
+  const LastTerm<TT, C> zero{};
   int none[8];
 #pragma unroll
   for (int d = 0; d < 8; ++d) none[d] = -1;
-  for (; l < L; ++l) put(l, z, none);
+  for (; l < L; ++l) put(l, zero.h, none, zero);
 }
 
 // ---------------------------------------------------------------------------

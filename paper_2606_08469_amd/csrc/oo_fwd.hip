@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const TreeArgs T, const flo
     }
     const int L = T.L;
     HT* hrow = h_out + (valid ? q : 0) * (int64_t)(L * C);
-    encode_paper<TT, C, MODE == 2>(T, valid, xq, s, t, [&](int l, const float (&h)[C], const int (&node)[8]) {
+    encode_paper<TT, C, MODE == 2>(T, valid, xq, s, t, [&](int l, const float* h, const int (&node)[8], auto&) {
       if (!valid) return;
       vC v;
 #pragma unroll
@@ -81,94 +81,6 @@ __global__ __launch_bounds__(256) void encode_kernel(const TreeArgs T, const flo
 }
 
 // ---------------------------------------------------------------------------
-// Fused query: encode 64 queries per wave into LDS, decode them there.
-// ---------------------------------------------------------------------------
-// Queries q < n_idx also store their node index per level in idx_out
-// (level-major [L][n_idx]) and their octahedral coordinates in uv_out, which
-// the residual backward reads instead of descending and mapping again.
-// In the paper's scheme the stored indices are the eight corner cells'
-// nodes per level ([L][8][n_idx]) and the query's position is kept too
-// (pos_out, [n_idx]); the backward recomputes the trilinear weights from it.
-// MODE as for encode_kernel; with the shift rgb[3 q] holds query q's
-// disparity when the kernel starts (the wave that reads it writes the
-// radiance there).
-template <class TT, class MT, int C, int H, bool WLDS, int MODE>
-__global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpArgs M, const QuerySrc src,
-                                                    int64_t Q, float* __restrict__ rgb, const QueryOut O) {
-  int32_t* __restrict__ idx_out = O.idx;
-  float2* __restrict__ uv_out = O.uv;
-  float4* __restrict__ pos_out = O.pos;
-  const int64_t n_idx = O.n_idx;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  // N-tiles per decoder pass: all four with 16-bit operands, LDS weights
-  // and 64-wide layers (each weight fragment read then serves four MFMAs;
-  // at width 128 the accumulators would spill)
-  constexpr int NT = sizeof(MT) == 2 && WLDS && H == 64 ? 4 : 2;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  const int KB0 = (M.K0 + 31) / 32;
-  const int wl_elems = WLDS ? packed_weight_elems<MT>(M.n_layers, M.K0, M.H) : 0;
-  float* const bias = reinterpret_cast<float*>(smem);
-  MT* wl = reinterpret_cast<MT*>(bias + bias_floats(M.n_layers, H));
-  MT* htile = wl + wl_elems + wave * (4 * KB0 * kWave * 8);
-  load_biases_lds(M, bias);
-  if (WLDS) pack_weights_lds<MT>(M, wl);
-  {  // zero the K padding of this lane's row once
-    const float z[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k = M.K0; k < 32 * KB0; k += 4) htile_put4<MT>(htile, KB0, lane, k, z);
-  }
-  __syncthreads();
-  const WFrag<MT, WLDS> W{wl, KB0};
-  const int64_t n_tiles = (Q + 63) / 64;
-  const TileRange tr = xcd_tiles(n_tiles, waves, wave);
-  for (int64_t tile = tr.first; tile < tr.end; tile += tr.stride) {
-    const int64_t q = tile * 64 + lane;
-    const bool valid = q < Q;
-    float x[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 1.f};
-    if (valid) load_query(src, q, x, d);
-    float s, t;
-    octa(d, s, t);
-    const bool keep = q < n_idx;
-    if (keep) uv_out[q] = make_float2(s, t);
-    if constexpr (MODE > 0) {
-      float u[3] = {0.f, 0.f, 0.f}, disp = 0.0f;
-      if constexpr (MODE >= 2) {
-        unit_dir3(d, u);
-        if (valid) disp = rgb[3 * q];
-      }
-      if (keep) pos_out[q] = make_float4(x[0], x[1], x[2], disp);
-      encode_paper<TT, C, MODE >= 2>(T, valid, x, s, t, [&](int l, const float (&h)[C], const int (&node)[8]) {
-#pragma unroll
-        for (int c = 0; c < C; c += 4) htile_put4<MT>(htile, KB0, lane, l * C + c, &h[c]);
-        if (keep)
-#pragma unroll
-          for (int d = 0; d < 8; ++d) idx_out[(l * 8 + d) * n_idx + q] = node[d];  // coalesced across lanes
-      }, disp, u);
-    } else {
-      encode_pipelined<TT, C>(T, valid, x, s, t, [&](int l, const float* h, int node) {
-#pragma unroll
-        for (int c = 0; c < C; c += 4) htile_put4<MT>(htile, KB0, lane, l * C + c, &h[c]);
-        if (keep) idx_out[l * n_idx + q] = node;  // level-major: coalesced across lanes
-      });
-    }
-    // the decoder's surface attributes follow the level features
-    for (int k = 0; k < M.E; k += 4) {
-      float g4[4] = {0.f, 0.f, 0.f, 0.f};
-      if (valid) load_attr4(src, q, k, g4);
-      htile_put4<MT>(htile, KB0, lane, M.K0 - M.E + k, g4);
-    }
-    wave_lds_sync();
-#pragma unroll
-    for (int t0 = 0; t0 < 4; t0 += NT) {
-      f32x4 out[NT];
-      mlp_forward_tiles<MT, H, NT, 0>(
-          M, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<MT>(htile, KB0, t0 + t, kb, lane); }, out);
-      store_rgb<NT>(out, tile * 64 + 16 * t0, Q, lane, rgb);
-    }
-    wave_lds_sync();
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Shifted encode of the residual's sorted queries into decoder input rows:
 // one thread per query (the paper's scheme with the disparity shift, each
 // query's disparity read from O.disp). Row q of h_rows (K0 = L C + E
@@ -199,7 +111,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C == 4 ? 4 
   }
   typedef MT vC __attribute__((ext_vector_type(C)));
   MT* const row = h_rows + (valid ? q : 0) * (int64_t)K0;
-  encode_paper<TT, C, true>(T, valid, x, s, t, [&](int l, const float (&h)[C], const int (&node)[8]) {
+  MT* const brow = keep ? reinterpret_cast<MT*>(O.rows) : nullptr;
+  typedef MT v4 __attribute__((ext_vector_type(4)));
+  encode_paper<TT, C, true>(T, valid, x, s, t, [&](int l, const float* h, const int (&node)[8], auto& last) {
     if (valid) {
       vC v;
 #pragma unroll
@@ -209,9 +123,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C == 4 ? 4 
     if (keep)
 #pragma unroll
       for (int dd = 0; dd < 8; ++dd) O.idx[(l * 8 + dd) * O.n_idx + q] = node[dd];  // coalesced across lanes
+    if constexpr (sizeof(MT) == 2)
+      if (brow)
+#pragma unroll
+        for (int c = 0; c < C; c += 4)
+          *reinterpret_cast<v4*>(brow + (((l * C + c) >> 2) * O.n_idx + q) * 4) = last.round4(c);
   }, disp, u);
   if (!valid) return;
-  typedef MT v4 __attribute__((ext_vector_type(4)));
   for (int k = 0; k < E; k += 4) {
     float g4[4];
     load_attr4(src, q, k, g4);
@@ -219,6 +137,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C == 4 ? 4 
 #pragma unroll
     for (int c = 0; c < 4; ++c) v[c] = from_f32<MT>(g4[c]);
     *reinterpret_cast<v4*>(row + K0 - E + k) = v;
+    if (brow) *reinterpret_cast<v4*>(brow + (((K0 - E + k) >> 2) * O.n_idx + q) * 4) = v;
   }
 }
 
@@ -400,94 +319,6 @@ hipError_t launch_encode(const TreeArgs& T, oo_dtype td, const float* x, const f
                     : launch_encode_h<f16, 8>(T, x, d, B, h, hd, idx, G, st);
   return T.C == 4 ? launch_encode_h<bf16, 4>(T, x, d, B, h, hd, idx, G, st)
                   : launch_encode_h<bf16, 8>(T, x, d, B, h, hd, idx, G, st);
-}
-
-// The shape without weights in LDS: as many 64-query tiles as fit, up to 8.
-template <class MT>
-static void tile_launch_shape_plain(const MlpArgs& M, int64_t Q, int& waves, size_t& lds, int& grid) {
-  const int KB0 = (M.K0 + 31) / 32;
-  const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
-  const size_t bb = bias_bytes(M);
-  waves = 8;
-  while (waves > 1 && bb + waves * tile_bytes > (size_t)max_lds()) --waves;
-  lds = bb + waves * tile_bytes;
-  grid = tile_grid((Q + 63) / 64, lds);
-}
-
-// Workgroup shape for the tile kernels: up to 8 waves, each with a 64-query
-// activation tile, plus the packed weights when they fit next to them.
-template <class MT>
-static void tile_launch_shape(const MlpArgs& M, int64_t Q, bool& wlds, int& waves, size_t& lds, int& grid) {
-  const int KB0 = (M.K0 + 31) / 32;
-  const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
-  const size_t wbytes = (size_t)packed_weight_elems<MT>(M.n_layers, M.K0, M.H) * sizeof(MT);
-  const size_t bb = bias_bytes(M);
-  const size_t cap = (size_t)max_lds() - bb;
-  waves = 8;
-  wlds = true;
-  while (waves > 4 && wbytes + waves * tile_bytes > cap) --waves;
-  if (wlds && wbytes + waves * tile_bytes > cap) wlds = false;
-  if (!wlds) {
-    waves = 8;
-    while (waves > 1 && waves * tile_bytes > cap) --waves;
-  }
-  lds = bb + (wlds ? wbytes : 0) + waves * tile_bytes;
-  grid = tile_grid((Q + 63) / 64, lds);
-}
-
-
-template <class TT, class MT, int C, int H, int MODE>
-static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
-                                 const QueryOut& O, hipStream_t st) {
-  bool wlds;
-  int waves, grid;
-  size_t lds;
-  tile_launch_shape<MT>(M, Q, wlds, waves, lds, grid);
-  if (wlds && MODE >= 2) {  // the shifted variants: keep one of each
-    wlds = false;
-    tile_launch_shape_plain<MT>(M, Q, waves, lds, grid);
-  }
-  if (wlds) {
-    auto k = query_kernel<TT, MT, C, H, true, MODE >= 2 ? 1 : MODE>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O);
-  } else {
-    auto k = query_kernel<TT, MT, C, H, false, MODE>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O);
-  }
-  return hipGetLastError();
-}
-
-template <class TT, class MT, int C, int H>
-static hipError_t launch_query_t(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
-                                 const QueryOut& O, const DispArgs& G, hipStream_t st) {
-  if (T.interp != OO_INTERP_PAPER) return launch_query_p<TT, MT, C, H, 0>(T, M, src, Q, rgb, O, st);
-  if (G.n_levels == 0) return launch_query_p<TT, MT, C, H, 1>(T, M, src, Q, rgb, O, st);
-  const hipError_t e = launch_predict(G, src, Q, rgb, 3, st);
-  if (e != hipSuccess) return e;
-  return launch_query_p<TT, MT, C, H, 2>(T, M, src, Q, rgb, O, st);
-}
-
-template <class TT, class MT, int C>
-static hipError_t launch_query_c(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
-                                 const QueryOut& O, const DispArgs& G, hipStream_t st) {
-  return M.H == 64 ? launch_query_t<TT, MT, C, 64>(T, M, src, Q, rgb, O, G, st)
-                   : launch_query_t<TT, MT, C, 128>(T, M, src, Q, rgb, O, G, st);
-}
-
-hipError_t launch_query(const TreeArgs& T, oo_dtype td, const MlpArgs& M, oo_dtype md, const QuerySrc& src,
-                        int64_t Q, float* rgb, const QueryOut& O, const DispArgs& G, hipStream_t st) {
-  if (Q == 0) return hipSuccess;
-  if (td == OO_F32)
-    return T.C == 4 ? launch_query_c<float, float, 4>(T, M, src, Q, rgb, O, G, st)
-                    : launch_query_c<float, float, 8>(T, M, src, Q, rgb, O, G, st);
-  if (td == OO_F16)
-    return T.C == 4 ? launch_query_c<f16, f16, 4>(T, M, src, Q, rgb, O, G, st)
-                    : launch_query_c<f16, f16, 8>(T, M, src, Q, rgb, O, G, st);
-  return T.C == 4 ? launch_query_c<bf16, bf16, 4>(T, M, src, Q, rgb, O, G, st)
-                  : launch_query_c<bf16, bf16, 8>(T, M, src, Q, rgb, O, G, st);
-  (void)md;
 }
 
 static int combine_group(int N) {

@@ -68,6 +68,7 @@ struct QueryOut {
   float4* pos;
   float4* wdir;
   int64_t n_idx;
+  void* rows = nullptr;         // 16-bit operands: the decoder's inputs, [K0 / 4][n_idx][4], for the backward
   const float* disp = nullptr;  // per-query disparity, read by the shifted encode into rows
 };
 // The predictor's d of Q queries into out[q * stride], in FP32 with every sum
@@ -83,8 +84,19 @@ hipError_t launch_disparity_fwd(const DispArgs& G, oo_dtype md, const QuerySrc& 
 // then the M.E surface attributes), with the backward's outputs in O.
 hipError_t launch_encode_rows(const TreeArgs& T, oo_dtype td, const MlpArgs& M, const QuerySrc& src, int64_t Q,
                               void* h_rows, const QueryOut& O, hipStream_t st);
-hipError_t launch_query(const TreeArgs& T, oo_dtype td, const MlpArgs& M, oo_dtype md, const QuerySrc& src,
-                        int64_t Q, float* rgb, const QueryOut& O, const DispArgs& G, hipStream_t st);
+// The tables and the decoder share one type.
+hipError_t launch_query_f32(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
+                            const QueryOut& O, const DispArgs& G, hipStream_t st);
+hipError_t launch_query_f16(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
+                            const QueryOut& O, const DispArgs& G, hipStream_t st);
+hipError_t launch_query_bf16(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
+                             const QueryOut& O, const DispArgs& G, hipStream_t st);
+inline hipError_t launch_query(const TreeArgs& T, oo_dtype md, const MlpArgs& M, const QuerySrc& src, int64_t Q,
+                               float* rgb, const QueryOut& O, const DispArgs& G, hipStream_t st) {
+  return md == OO_F32   ? launch_query_f32(T, M, src, Q, rgb, O, G, st)
+         : md == OO_F16 ? launch_query_f16(T, M, src, Q, rgb, O, G, st)
+                        : launch_query_bf16(T, M, src, Q, rgb, O, G, st);
+}
 
 // Spatial bucketing of the residual queries: NB chunks, K buckets (octree
 // cell level c). Workspace: counts [NB][K], total [K], start [K] int32;
@@ -107,13 +119,13 @@ hipError_t launch_saved_nodes(const int32_t* nidx, const int32_t* order, int64_t
 
 // Backward.
 int bwd_grid(const MlpArgs& M, oo_dtype md, int L, int64_t Q);
-size_t bwd_lds_bytes(const MlpArgs& M, oo_dtype md, int L);
+// Seeds of the Qb backward queries in sorted order (source query order[p]).
 hipError_t launch_seeds(const ResidualArgs& A, const float* resid, const float* rhs, const double* grad_loss,
-                        int full, float* seeds, hipStream_t st);
+                        const int32_t* order, int64_t Qb, float* seeds, hipStream_t st);
 hipError_t launch_transpose_weights(const MlpArgs& M, oo_dtype md, void* const* Wt, hipStream_t st);
 // One backward launch over Q consecutive sorted positions: node indices
-// nidx[l * ldn + q], coordinates uv[q], order[q] (source query, whose seed
-// row is read if it is below n_seed), dh[q][K0] out, one dW/db partial per
+// nidx[l * ldn + q], coordinates uv[q], order[q] (source query), seeds[q],
+// dh[q][K0] out, one dW/db partial per
 // workgroup into partials [grid][P] (added to what is there when
 // accumulate is set).
 struct BwdArgs {
@@ -122,12 +134,12 @@ struct BwdArgs {
   int64_t ldn;
   const float2* uv;
   const float4* pos;    // the paper's scheme: query positions, [Q]
-  const float* seeds;
+  const float* seeds;   // [Q][3]
   const int32_t* order;
-  int64_t n_seed;
   float* partials;
   float* dh;            // [Q][L C]: dLoss/dh of the level features
   int accumulate;
+  const void* rows = nullptr;  // 16-bit operands: the decoder's inputs that the forward kept, [K0 / 4][ldn][4]
   // the decoder's surface attributes in the caller's query order: [nA][E]
   // for the first nA queries, [n_src - nA][E] for the rest
   const float* gA = nullptr;
@@ -138,6 +150,13 @@ struct BwdArgs {
   const float4* wdir = nullptr;
   int shift = 0;
 };
+// The same with 16-bit operands, where bwd16_shape has a workgroup for it
+// (no tables and no transposed weights needed).
+hipError_t launch_bwd16(const MlpArgs& M, oo_dtype md, int LC, const BwdArgs& A, const ParamLayout& PL, int grid,
+                        hipStream_t st);
+// Whether this decoder's backward runs there; the others read transposed
+// weight copies and gather the features again.
+bool runs_bwd16(const MlpArgs& M, oo_dtype md);
 hipError_t launch_bwd(const TreeArgs& T, oo_dtype td, const MlpArgs& M, oo_dtype md, void* const* Wt,
                       const BwdArgs& A, const ParamLayout& PL, int grid, hipStream_t st);
 // Feature-gradient scatter. With the disparity shift (wdir set; the

@@ -1,0 +1,214 @@
+// The fused query kernel (oo_query_fwd, and the residual forward's queries),
+// instantiated for one decoder type per source file.
+#pragma once
+
+#include "oo_mlp.h"
+
+namespace oo {
+
+// ---------------------------------------------------------------------------
+// Fused query: encode 64 queries per wave into LDS, decode them there.
+// ---------------------------------------------------------------------------
+// Queries q < n_idx also store their node index per level in idx_out
+// (level-major [L][n_idx]) and their octahedral coordinates in uv_out, which
+// the residual backward reads instead of descending and mapping again.
+// In the paper's scheme the stored indices are the eight corner cells'
+// nodes per level ([L][8][n_idx]) and the query's position is kept too
+// (pos_out, [n_idx]); the scatter recomputes the trilinear weights from it.
+// With 16-bit operands the decoder's inputs are kept as well (O.rows,
+// [K0 / 4][n_idx][4]: a wave's stores are contiguous), so that the backward
+// gathers nothing.
+// MODE as for encode_kernel; with the shift rgb[3 q] holds query q's
+// disparity when the kernel starts (the wave that reads it writes the
+// radiance there).
+// KEEP: the queries of this launch are the backward's (q < n_idx). The
+// residual forward runs the others in a launch of their own, without the
+// stores.
+template <class MT, int C, int H, bool WLDS, int MODE, bool KEEP>
+__global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpArgs M, const QuerySrc src,
+                                                    int64_t Q, float* __restrict__ rgb, const QueryOut O) {
+  int32_t* __restrict__ idx_out = O.idx;
+  float2* __restrict__ uv_out = O.uv;
+  float4* __restrict__ pos_out = O.pos;
+  const int64_t n_idx = O.n_idx;
+  MT* const brows = reinterpret_cast<MT*>(O.rows);
+  typedef MT v4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // N-tiles per decoder pass: all four with 16-bit operands, LDS weights
+  // and 64-wide layers (each weight fragment read then serves four MFMAs;
+  // at width 128 the accumulators would spill)
+  constexpr int NT = sizeof(MT) == 2 && WLDS && H == 64 ? 4 : 2;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int KB0 = (M.K0 + 31) / 32;
+  const int wl_elems = WLDS ? packed_weight_elems<MT>(M.n_layers, M.K0, M.H) : 0;
+  float* const bias = reinterpret_cast<float*>(smem);
+  MT* wl = reinterpret_cast<MT*>(bias + bias_floats(M.n_layers, H));
+  MT* htile = wl + wl_elems + wave * (4 * KB0 * kWave * 8);
+  load_biases_lds(M, bias);
+  if (WLDS) pack_weights_lds<MT>(M, wl);
+  {  // zero the K padding of this lane's row once
+    const float z[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int k = M.K0; k < 32 * KB0; k += 4) htile_put4<MT>(htile, KB0, lane, k, z);
+  }
+  __syncthreads();
+  const WFrag<MT, WLDS> W{wl, KB0};
+  const int64_t n_tiles = (Q + 63) / 64;
+  const TileRange tr = xcd_tiles(n_tiles, waves, wave);
+  for (int64_t tile = tr.first; tile < tr.end; tile += tr.stride) {
+    const int64_t q = tile * 64 + lane;
+    const bool valid = q < Q;
+    float x[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 1.f};
+    if (valid) load_query(src, q, x, d);
+    float s, t;
+    octa(d, s, t);
+    const bool keep = KEEP && valid;
+    if (keep) uv_out[q] = make_float2(s, t);
+    if constexpr (MODE > 0) {
+      float u[3] = {0.f, 0.f, 0.f}, disp = 0.0f;
+      if constexpr (MODE >= 2) {
+        unit_dir3(d, u);
+        if (valid) disp = rgb[3 * q];
+      }
+      if (keep) pos_out[q] = make_float4(x[0], x[1], x[2], disp);
+      encode_paper<MT, C, MODE >= 2>(T, valid, x, s, t, [&](int l, const float* h, const int (&node)[8], auto& last) {
+#pragma unroll
+        for (int c = 0; c < C; c += 4) htile_put4<MT>(htile, KB0, lane, l * C + c, &h[c]);
+        if (keep) {
+#pragma unroll
+          for (int d = 0; d < 8; ++d) idx_out[(l * 8 + d) * n_idx + q] = node[d];  // coalesced across lanes
+          if constexpr (sizeof(MT) == 2)
+            if (brows)
+#pragma unroll
+              for (int c = 0; c < C; c += 4)
+                *reinterpret_cast<v4*>(brows + (((l * C + c) >> 2) * n_idx + q) * 4) = last.round4(c);
+        }
+      }, disp, u);
+    } else {
+      encode_pipelined<MT, C>(T, valid, x, s, t, [&](int l, const float* h, int node, auto& last) {
+#pragma unroll
+        for (int c = 0; c < C; c += 4) htile_put4<MT>(htile, KB0, lane, l * C + c, &h[c]);
+        if (keep) {
+          idx_out[l * n_idx + q] = node;  // level-major: coalesced across lanes
+          if constexpr (sizeof(MT) == 2)
+            if (brows)
+#pragma unroll
+              for (int c = 0; c < C; c += 4)
+                *reinterpret_cast<v4*>(brows + (((l * C + c) >> 2) * n_idx + q) * 4) = last.round4(c);
+        }
+      });
+    }
+    // the decoder's surface attributes follow the level features
+    for (int k = 0; k < M.E; k += 4) {
+      float g4[4] = {0.f, 0.f, 0.f, 0.f};
+      if (valid) load_attr4(src, q, k, g4);
+      htile_put4<MT>(htile, KB0, lane, M.K0 - M.E + k, g4);
+      if (sizeof(MT) == 2 && keep && brows) {
+        v4 v;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = from_f32<MT>(g4[c]);
+        *reinterpret_cast<v4*>(brows + (((M.K0 - M.E + k) >> 2) * n_idx + q) * 4) = v;
+      }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int t0 = 0; t0 < 4; t0 += NT) {
+      f32x4 out[NT];
+      mlp_forward_tiles<MT, H, NT, 0>(
+          M, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<MT>(htile, KB0, t0 + t, kb, lane); }, out);
+      store_rgb<NT>(out, tile * 64 + 16 * t0, Q, lane, rgb);
+    }
+    wave_lds_sync();
+  }
+}
+
+// The shape without weights in LDS: as many 64-query tiles as fit, up to 8.
+template <class MT>
+static void tile_launch_shape_plain(const MlpArgs& M, int64_t Q, int& waves, size_t& lds, int& grid) {
+  const int KB0 = (M.K0 + 31) / 32;
+  const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
+  const size_t bb = bias_bytes(M);
+  waves = 8;
+  while (waves > 1 && bb + waves * tile_bytes > (size_t)max_lds()) --waves;
+  lds = bb + waves * tile_bytes;
+  grid = tile_grid((Q + 63) / 64, lds);
+}
+
+// Workgroup shape for the tile kernels: up to 8 waves, each with a 64-query
+// activation tile, plus the packed weights when they fit next to them.
+template <class MT>
+static void tile_launch_shape(const MlpArgs& M, int64_t Q, bool& wlds, int& waves, size_t& lds, int& grid) {
+  const int KB0 = (M.K0 + 31) / 32;
+  const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
+  const size_t wbytes = (size_t)packed_weight_elems<MT>(M.n_layers, M.K0, M.H) * sizeof(MT);
+  const size_t bb = bias_bytes(M);
+  const size_t cap = (size_t)max_lds() - bb;
+  waves = 8;
+  wlds = true;
+  while (waves > 4 && wbytes + waves * tile_bytes > cap) --waves;
+  if (wlds && wbytes + waves * tile_bytes > cap) wlds = false;
+  if (!wlds) {
+    waves = 8;
+    while (waves > 1 && waves * tile_bytes > cap) --waves;
+  }
+  lds = bb + (wlds ? wbytes : 0) + waves * tile_bytes;
+  grid = tile_grid((Q + 63) / 64, lds);
+}
+
+
+template <class MT, int C, int H, int MODE, bool KEEP>
+static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
+                                 const QueryOut& O, hipStream_t st) {
+  bool wlds;
+  int waves, grid;
+  size_t lds;
+  tile_launch_shape<MT>(M, Q, wlds, waves, lds, grid);
+  if (wlds && MODE >= 2) {  // the shifted variants: keep one of each
+    wlds = false;
+    tile_launch_shape_plain<MT>(M, Q, waves, lds, grid);
+  }
+  if (wlds) {
+    auto k = query_kernel<MT, C, H, true, MODE >= 2 ? 1 : MODE, KEEP>;
+    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O);
+  } else {
+    auto k = query_kernel<MT, C, H, false, MODE, KEEP>;
+    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O);
+  }
+  return hipGetLastError();
+}
+
+template <class MT, int C, int H>
+static hipError_t launch_query_t(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
+                                 const QueryOut& O, const DispArgs& G, hipStream_t st) {
+  if (T.interp == OO_INTERP_PAPER && G.n_levels > 0) {
+    const hipError_t e = launch_predict(G, src, Q, rgb, 3, st);
+    return e != hipSuccess ? e : launch_query_p<MT, C, H, 2, false>(T, M, src, Q, rgb, O, st);
+  }
+  const bool paper = T.interp == OO_INTERP_PAPER;
+  if (O.n_idx > 0) {
+    const int64_t n = O.n_idx < Q ? O.n_idx : Q;
+    const hipError_t e = paper ? launch_query_p<MT, C, H, 1, true>(T, M, src, n, rgb, O, st)
+                               : launch_query_p<MT, C, H, 0, true>(T, M, src, n, rgb, O, st);
+    if (e != hipSuccess || n == Q) return e;
+    QuerySrc rest = src;  // sorted positions n ..
+    rest.idx += n;
+    return paper ? launch_query_p<MT, C, H, 1, false>(T, M, rest, Q - n, rgb + 3 * n, O, st)
+                 : launch_query_p<MT, C, H, 0, false>(T, M, rest, Q - n, rgb + 3 * n, O, st);
+  }
+  return paper ? launch_query_p<MT, C, H, 1, false>(T, M, src, Q, rgb, O, st)
+               : launch_query_p<MT, C, H, 0, false>(T, M, src, Q, rgb, O, st);
+}
+
+template <class MT>
+hipError_t launch_query_m(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
+                          const QueryOut& O, const DispArgs& G, hipStream_t st) {
+  if (Q == 0) return hipSuccess;
+  if (T.C == 4)
+    return M.H == 64 ? launch_query_t<MT, 4, 64>(T, M, src, Q, rgb, O, G, st)
+                     : launch_query_t<MT, 4, 128>(T, M, src, Q, rgb, O, G, st);
+  return M.H == 64 ? launch_query_t<MT, 8, 64>(T, M, src, Q, rgb, O, G, st)
+                   : launch_query_t<MT, 8, 128>(T, M, src, Q, rgb, O, G, st);
+}
+
+}  // namespace oo
