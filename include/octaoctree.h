@@ -327,8 +327,11 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
                               void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 /*
- * Residual backward. The texel gathers and the decoder forward are
- * recomputed, not stored; the node index per level comes from the forward.
+ * Residual backward. The decoder forward is recomputed from its inputs. With
+ * a 16-bit decoder whose backward runs from LDS (every accepted one but four
+ * 128-wide hidden layers over more than 96 inputs) the forward keeps those
+ * inputs in the workspace, 2 bytes each per query; else the texel gathers are
+ * repeated too, from the node index per level that the forward kept.
  *  - workspace: the one the forward of this batch used, unchanged since.
  *    The forward leaves there the bucketed query order and, for every query
  *    the backward processes, its node indices and octahedral coordinates.

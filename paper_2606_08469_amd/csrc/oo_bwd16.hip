@@ -17,6 +17,15 @@
 // i % 4 of what lanes i / 4, 4 + i / 4, 8 + i / 4 and 12 + i / 4 address.
 // The same read turns a layer's activations, stored as the operands they
 // are, into the [neuron][queries] operands of dW.
+//
+// Bound by LDS reads and the two barriers per layer; the matrix cores are a
+// third busy. 262,144 queries, 88 features, two 128-wide hidden layers in FP16:
+// 96 us, where one kernel that shared 64 queries between its waves and gathered
+// the features again took 335 us; 32,768 queries, 48 inputs, four 128-wide
+// layers: 63 us after 403 us. A bias sum needs
+// an accumulator of its own per layer: one shared by all layers, a column
+// each, is 1% faster but lets an infinite delta of one layer make the others'
+// sums NaN (zero times infinity).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -10,6 +10,7 @@ import oracle
 from paper_2606_08469_amd import binding, synth
 
 from _gpu import rel_l2, report, to_np
+from _tiny import tiny_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -119,3 +120,77 @@ def test_shifted_query_refuses_short_workspace():
         assert L.oo_query_fwd_ws(ctypes.byref(ts), ctypes.byref(ms), p(x), p(x), p(attr), 100, p(rgb), w, size, None) == -1
     torch.cuda.synchronize()
     assert torch.all(rgb == 7.0)
+
+
+@pytest.mark.parametrize("widths,n_attr", [((64,), 0), ((64, 64, 64, 64), 112), ((128,), 4), ((128, 128), 8),
+                                           ((128, 128), 112), ((128, 128, 128), 48), ((128,) * 4, 32),
+                                           ((128,) * 4, 72), ((128,) * 4, 112)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("B", [1, 17, 129, 700])
+def test_decoder_backward_shapes(widths, n_attr, dtype, B):
+    """Every workgroup shape of the 16-bit backward: no to three
+    hidden-to-hidden layers, four or eight waves, exchange buffers for all or
+    a share of the waves, and the widest decoder, which runs the kernel with
+    weights in L2; batches that end inside a tile and inside a wave's 16
+    queries. Loss and weight gradients against plain FP64 torch that rounds
+    inputs, activations, seeds and deltas to 16 bits where the kernel does.
+    What is left is FP32 sums that round to the other 16-bit neighbour, now
+    and then, in up to five layers: 10 units of 2^-11 (2^-8 for BF16)."""
+    tree, mlp, bt = tiny_problem(seed=5, widths=widths, B=max(B, 2), N=0, n_attr=n_attr, bias_scale=0.1)
+    bt = {k: (v[:B] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
+    bt["target_override"] = np.random.default_rng(1).uniform(0, 1, (B, 3)).astype(np.float32)
+    print(f"[case] backward {widths} E={n_attr} {dtype} B={B}", flush=True)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, tree.res, tree.C, tree.feat, mlp.W, mlp.b, dtype=dtype)
+    dev = binding.device_batch(bt)
+    loss = model.residual(dev)
+    loss.backward()
+    h, _ = binding.encode_query(model.tree, dev["x"], dev["dir"], dtype, feat=model.work_feat)
+    r16 = lambda t: t.to(dtype).double()
+    a = [h.double() if n_attr == 0 else torch.cat([h.double(), r16(dev["attr"])], 1)]
+    W = [w.double() for w in model.work_W]
+    b = [v.detach().double() for v in model.b]
+    z = []
+    for i in range(len(W) - 1):
+        z.append(a[-1] @ W[i].T + b[i])
+        a.append(r16(z[i].relu()))
+    res = a[-1] @ W[-1].T + b[-1] - dev["target_override"].double()
+    want = (res * res).sum() / (3 * B)
+    bar = 10 * (2.0 ** -11 if dtype == torch.float16 else 2.0 ** -8)
+
+    def error(open_):
+        d = r16(2 * res)
+        worst = abs(float(loss.detach()) / float(want) - 1)
+        for i in reversed(range(len(W))):
+            for got, ref in ((model.W[i].grad, d.T @ a[i] / (3 * B)), (model.b[i].grad, d.sum(0) / (3 * B))):
+                if ref.norm() > 0:
+                    worst = max(worst, float((got.double() - ref).norm() / ref.norm()))
+            if i:
+                d = r16((d @ W[i]) * open_[i - 1])
+        dh = (d @ W[0])[:, :tree.n_levels * tree.C] / (3 * B)
+        # a level's map entries collect dh with weights that sum to one per query
+        for l, f in enumerate(model.feat):
+            has = torch.from_numpy(oracle.descend(tree, bt["x"])[:, l] >= 0).cuda()
+            ref = (dh[:, l * tree.C:(l + 1) * tree.C] * has[:, None]).sum(0)
+            got = f.grad.double().sum((0, 1, 2))
+            scale = (dh[:, l * tree.C:(l + 1) * tree.C] * has[:, None]).abs().sum(0).norm()
+            if scale > 0:
+                worst = max(worst, float((got - ref).norm() / scale))
+        return worst
+
+    # A unit whose sum lies nearer to zero than one input's rounding to its
+    # other neighbour moves it has no one derivative: the kernel may take
+    # either side, and the reference goes along with it, the nearest first.
+    open_ = [x > 0 for x in a[1:]]
+    worst = error(open_)
+    if worst > bar:
+        near = [(float(z[i][q, n].abs()), i, q, n) for i in range(len(z)) for q, n in
+                (z[i].abs() < bar / 10 * (a[i][:, None] * W[i]).abs().amax(-1)).nonzero().tolist()]
+        for _, i, q, n in sorted(near)[:64]:
+            open_[i][q, n] ^= True
+            e = error(open_)
+            if e < worst:
+                worst = e
+            else:
+                open_[i][q, n] ^= True
+    report(f"backward {widths} E={n_attr} {dtype} B={B}", worst=worst)
+    assert worst <= bar
