@@ -407,7 +407,7 @@ Workspace workspace_layout(const MlpArgs& M, oo_dtype md, const oo_residual_batc
   w.dwp = o;  // dW/db partials, [grid][P], accumulated over the backward's chunks
   o = align256(o + (size_t)w.grid * w.PL.P * sizeof(float));
   // spatially bucketed queries, written by the forward and read by both passes
-  const SortShape ss = sort_shape(Qf, L - 1);
+  const SortShape ss = sort_shape(Qf, L - 1, shift);
   w.order = o;
   o = align256(o + (size_t)Qf * sizeof(int32_t));
   w.rank = o;
@@ -726,7 +726,7 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
     ProfScope ps(OO_PROF_SORT, stream);
     e = launch_spatial_sort(src, Q, A.B, tree->n_levels - 1, reinterpret_cast<int32_t*>(ws + w.scount),
                             reinterpret_cast<int32_t*>(ws + w.stotal), reinterpret_cast<int32_t*>(ws + w.sstart),
-                            order, rank, stream);
+                            order, rank, Lq, G.n_levels > 0, stream);
   }
   if (e != hipSuccess) return hip_status(e, "query bucketing launch");
   QuerySrc sorted = src;

@@ -101,14 +101,16 @@ inline hipError_t launch_query(const TreeArgs& T, oo_dtype md, const MlpArgs& M,
 // Spatial bucketing of the residual queries: NB chunks, K buckets (octree
 // cell level c). Workspace: counts [NB][K], total [K], start [K] int32;
 // outputs order [Q] (source query of each sorted position) and rank [Q]
-// (sorted position of each source query).
+// (sorted position of each source query). fine: sorted by level F > c within
+// runs of positions, with scratch of 8 Q bytes (free again afterwards).
 struct SortShape {
-  int c, K, NB;
+  int c, F, K, NB;
   int64_t chunk;
 };
-SortShape sort_shape(int64_t Q, int D);
+SortShape sort_shape(int64_t Q, int D, bool fine);
 hipError_t launch_spatial_sort(const QuerySrc& src, int64_t Q, int64_t n_lhs, int D, int32_t* counts, int32_t* total,
-                               int32_t* start, int32_t* order, int32_t* rank, hipStream_t st);
+                               int32_t* start, int32_t* order, int32_t* rank, void* scratch, bool fine,
+                               hipStream_t st);
 int combine_blocks(int64_t B, int N);
 // Lq row of query q is rank[q] when rank is set, else q.
 hipError_t launch_combine(const ResidualArgs& A, const float* Lq, const int32_t* rank, float* lhs, float* rhs,

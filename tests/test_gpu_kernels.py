@@ -194,3 +194,41 @@ def test_decoder_backward_shapes(widths, n_attr, dtype, B):
                 open_[i][q, n] ^= True
     report(f"backward {widths} E={n_attr} {dtype} B={B}", worst=worst)
     assert worst <= bar
+
+
+@pytest.mark.parametrize("D", [4, 5, 7])
+@pytest.mark.parametrize("B,N", [(1, 0), (262143, 0), (262144, 0), (270001, 0), (40000, 6), (5000, 60)])
+def test_shifted_residual_query_order(D, B, N):
+    """The finer query order of the shifted residual (tree depths where it has
+    no, one and two levels to add; batches around the smallest it takes; runs
+    that end early; more buckets in a run
+    than have ranks of their own, since the points fill the cube): a query's
+    result does not depend on where it is evaluated, so permuting the batch
+    permutes every output, bit for bit, and the corner nodes."""
+    res = (8, 8, 4, 4, 2, 2, 2, 2)[:D + 1]
+    tree, _, _ = tiny_problem(seed=3, D=D, res=res, B=2, N=0)
+    g = np.random.default_rng(11)
+    bt = tiny_problem(seed=4, D=D, res=res, B=max(B, 2), N=N, widths=(64,), n_attr=0)[2]
+    bt = {k: (v[:B] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
+    bt["x"] = g.uniform(0, 1, (B, 3)).astype(np.float32)
+    if N == 0:
+        bt["target_override"] = g.uniform(0, 1, (B, 3)).astype(np.float32)
+    feat = [g.normal(0, 0.1, (len(f), r + 1, r + 1, 4)).astype(np.float32) for f, r in zip(tree.feat, res)]
+    W = [g.uniform(-0.3, 0.3, s).astype(np.float32) for s in ((64, 4 * (D + 1)), (3, 64))]
+    b = [np.zeros(s, np.float32) for s in (64, 3)]
+    disp = synth.init_disparity(synth.CONFIGS[6], log2_T=10, table_scale=0.5, d0=1.5)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, list(res), 4, feat, W, b, dtype=torch.float16,
+                               interp=binding.INTERP_PAPER, disparity=disp)
+    print(f"[case] query order D={D} B={B} N={N}", flush=True)
+
+    def run(batch):
+        dev = binding.device_batch(batch)
+        ws = model.workspace(dev)
+        lhs, rhs, resid, loss = binding.residual_fwd(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)
+        idx = binding.residual_node_indices(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)
+        return [to_np(t) for t in (lhs, rhs, resid, idx)]
+
+    p = g.permutation(B)
+    moved = {k: (v[p] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
+    for name, u, v in zip(("lhs", "rhs", "resid", "idx"), run(bt), run(moved)):
+        assert np.array_equal(u[p], v), name
