@@ -57,44 +57,15 @@ __device__ inline f32x4 bias_tile(const float* bias, int m, int lane) {
   return *reinterpret_cast<const f32x4*>(bias + 16 * m + 4 * (lane >> 4));
 }
 
-// Runs the MLP on NT N-tiles of 16 queries and returns the output tile per
-// N-tile (rows 0..2 = RGB in lanes 0..15). input(kb, t) is the B operand of
-// the first layer: K-chunk kb < KB0 of N-tile t. The bias is the C operand of
-// a layer's first MFMA, so no accumulator is copied or initialised.
-// KB is KB0 where the caller knows it at compile time, else 0.
-template <class MT, int H, int NT, int KB, class WSrc, class In>
-__device__ inline void mlp_forward_tiles(const MlpArgs& M, const WSrc& W, const float* bias, int KB0, int lane,
-                                         In&& input, f32x4 out[NT]) {
-  // M is a kernel argument: indexing its arrays reads the argument segment.
+// The layers after the first on NT N-tiles of 16 queries: acc holds the first
+// layer's sums (before its ReLU), out gets the output tile per N-tile (rows
+// 0..2 = RGB in lanes 0..15). The bias is the C operand of a layer's first
+// MFMA, so no accumulator is copied or initialised.
+template <class MT, int H, int NT, class WSrc>
+__device__ inline void mlp_rest(const MlpArgs& M, const WSrc& W, const float* bias, int lane,
+                                f32x4 (&acc)[H / 16][NT], f32x4 out[NT]) {
   typedef typename FragT<MT>::type frag;
   constexpr int MH = H / 16, KH = H / 32;
-  f32x4 acc[MH][NT];
-  // layer 0: K0 -> H. Each K-chunk's weight fragments are all read before
-  // its MFMAs, so their LDS latency overlaps instead of stalling every pair
-  // of MFMAs.
-  auto chunk = [&](int kb, bool first) {
-    frag bf[NT], a[MH];
-    f32x4 bt[MH];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) bf[t] = input(kb, t);
-#pragma unroll
-    for (int m = 0; m < MH; ++m) {
-      a[m] = W.get(M, 0, m, kb, lane);
-      if (first) bt[m] = bias_tile(bias, m, lane);
-    }
-    __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink each read to its MFMAs)
-#pragma unroll
-    for (int m = 0; m < MH; ++m)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[m][t] = mma(a[m], bf[t], first ? bt[m] : acc[m][t]);
-  };
-  chunk(0, true);
-  if constexpr (KB > 0) {
-#pragma unroll
-    for (int kb = 1; kb < KB; ++kb) chunk(kb, false);
-  } else {
-    for (int kb = 1; kb < KB0; ++kb) chunk(kb, false);
-  }
   // hidden layers H -> H
   for (int layer = 1; layer < M.n_layers - 1; ++layer) {
     const float* lb = bias + layer * H;
@@ -129,6 +100,46 @@ __device__ inline void mlp_forward_tiles(const MlpArgs& M, const WSrc& W, const 
     for (int t = 0; t < NT; ++t)
       out[t] = mma(a, chain_frag<MT>(acc[2 * kb][t], acc[2 * kb + 1][t], true), kb == 0 ? bt : out[t]);
   }
+}
+
+// Runs the MLP on NT N-tiles of 16 queries and returns the output tile per
+// N-tile. input(kb, t) is the B operand of the first layer: K-chunk kb < KB0
+// of N-tile t.
+// KB is KB0 where the caller knows it at compile time, else 0.
+template <class MT, int H, int NT, int KB, class WSrc, class In>
+__device__ inline void mlp_forward_tiles(const MlpArgs& M, const WSrc& W, const float* bias, int KB0, int lane,
+                                         In&& input, f32x4 out[NT]) {
+  // M is a kernel argument: indexing its arrays reads the argument segment.
+  typedef typename FragT<MT>::type frag;
+  constexpr int MH = H / 16;
+  f32x4 acc[MH][NT];
+  // layer 0: K0 -> H. Each K-chunk's weight fragments are all read before
+  // its MFMAs, so their LDS latency overlaps instead of stalling every pair
+  // of MFMAs.
+  auto chunk = [&](int kb, bool first) {
+    frag bf[NT], a[MH];
+    f32x4 bt[MH];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) bf[t] = input(kb, t);
+#pragma unroll
+    for (int m = 0; m < MH; ++m) {
+      a[m] = W.get(M, 0, m, kb, lane);
+      if (first) bt[m] = bias_tile(bias, m, lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink each read to its MFMAs)
+#pragma unroll
+    for (int m = 0; m < MH; ++m)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[m][t] = mma(a[m], bf[t], first ? bt[m] : acc[m][t]);
+  };
+  chunk(0, true);
+  if constexpr (KB > 0) {
+#pragma unroll
+    for (int kb = 1; kb < KB; ++kb) chunk(kb, false);
+  } else {
+    for (int kb = 1; kb < KB0; ++kb) chunk(kb, false);
+  }
+  mlp_rest<MT, H, NT>(M, W, bias, lane, acc, out);
 }
 
 // Packs every layer's weights in fragment order: put(f, lane, frag) gets

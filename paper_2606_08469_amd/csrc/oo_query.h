@@ -21,12 +21,35 @@ namespace oo {
 // MODE as for encode_kernel; with the shift rgb[3 q] holds query q's
 // disparity when the kernel starts (the wave that reads it writes the
 // radiance there).
+// Streaming (64-wide layers with the weights in LDS): the first layer takes
+// the inputs chunk by chunk while the gathers of the next levels are in
+// flight, so a wave's tile holds one chunk of 32 and the LDS holds more waves:
+// gathers, conversions and MFMAs of different waves overlap. 1280x720 queries,
+// 72 inputs, three hidden layers: FP32 two or three waves per SIMD in place of
+// one, 309 -> 282 us; FP16 four in place of two, 72 -> 68 us (144 registers,
+// which allow three only, 73 us). At width 128 the sums of the first layer
+// alone take 128 registers, which leaves the two waves that whole tiles
+// allow too.
+constexpr bool query_streams(int H, bool wlds) { return H == 64 && wlds; }
+// Waves per workgroup: FP32 takes one workgroup per CU, up to twelve waves
+// where the registers (168) do without scratch memory to speak of, 16-bit two
+// of eight waves (128 registers).
+template <class MT>
+constexpr int query_waves(int H, bool wlds, int mode) {
+  return query_streams(H, wlds) && mode == 0 && sizeof(MT) == 4 ? 12 : 8;
+}
+template <class MT>
+constexpr int query_waves_per_simd(int H, bool wlds, int mode) {
+  return query_waves<MT>(H, wlds, mode) / 4 * (query_streams(H, wlds) && sizeof(MT) == 2 ? 2 : 1);
+}
+
 // KEEP: the queries of this launch are the backward's (q < n_idx). The
 // residual forward runs the others in a launch of their own, without the
 // stores.
 template <class MT, int C, int H, bool WLDS, int MODE, bool KEEP>
-__global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpArgs M, const QuerySrc src,
-                                                    int64_t Q, float* __restrict__ rgb, const QueryOut O) {
+__global__ __launch_bounds__(64 * query_waves<MT>(H, WLDS, MODE))
+    __attribute__((amdgpu_waves_per_eu(query_waves_per_simd<MT>(H, WLDS, MODE)))) void query_kernel(
+    const TreeArgs T, const MlpArgs M, const QuerySrc src, int64_t Q, float* __restrict__ rgb, const QueryOut O) {
   int32_t* __restrict__ idx_out = O.idx;
   float2* __restrict__ uv_out = O.uv;
   float4* __restrict__ pos_out = O.pos;
@@ -40,13 +63,16 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
   constexpr int NT = sizeof(MT) == 2 && WLDS && H == 64 ? 4 : 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
   const int KB0 = (M.K0 + 31) / 32;
+  constexpr bool STREAM = query_streams(H, WLDS);
+  constexpr int MH = H / 16;
+  const int KBT = STREAM ? 1 : KB0;  // chunks the wave's tile holds
   const int wl_elems = WLDS ? packed_weight_elems<MT>(M.n_layers, M.K0, M.H) : 0;
   float* const bias = reinterpret_cast<float*>(smem);
   MT* wl = reinterpret_cast<MT*>(bias + bias_floats(M.n_layers, H));
-  MT* htile = wl + wl_elems + wave * (4 * KB0 * kWave * 8);
+  MT* htile = wl + wl_elems + wave * (4 * KBT * kWave * 8);
   load_biases_lds(M, bias);
   if (WLDS) pack_weights_lds<MT>(M, wl);
-  {  // zero the K padding of this lane's row once
+  if (!STREAM) {  // zero the K padding of this lane's row once
     const float z[4] = {0.f, 0.f, 0.f, 0.f};
     for (int k = M.K0; k < 32 * KB0; k += 4) htile_put4<MT>(htile, KB0, lane, k, z);
   }
@@ -62,6 +88,38 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
     float s, t;
     octa(d, s, t);
     const bool keep = KEEP && valid;
+    f32x4 acc0[STREAM ? MH : 1][4];  // the first layer's sums
+    if constexpr (STREAM) {
+#pragma unroll
+      for (int m = 0; m < MH; ++m) {
+        const f32x4 b = bias_tile(bias, m, lane);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc0[m][t] = b;
+      }
+    }
+    // Inputs k .. k + 3 of this lane's query, in the order of k. Streaming,
+    // each full chunk of 32 goes through the first layer at once.
+    auto input4 = [&](int k, const float* v) {
+      htile_put4<MT>(htile, KBT, lane, STREAM ? k & 31 : k, v);
+      if constexpr (STREAM) {
+        if ((k & 31) != 28) return;
+        wave_lds_sync();
+#pragma unroll
+        for (int t0 = 0; t0 < 4; t0 += NT) {
+          typename FragT<MT>::type b[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) b[t] = htile_get<MT>(htile, 1, t0 + t, 0, lane);
+#pragma unroll
+          for (int m = 0; m < MH; ++m) {
+            const auto a = W.get(M, 0, m, k >> 5, lane);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc0[m][t0 + t] = mma(a, b[t], acc0[m][t0 + t]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_lds_sync();
+      }
+    };
     if (keep) uv_out[q] = make_float2(s, t);
     if constexpr (MODE > 0) {
       float u[3] = {0.f, 0.f, 0.f}, disp = 0.0f;
@@ -72,7 +130,7 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
       if (keep) pos_out[q] = make_float4(x[0], x[1], x[2], disp);
       encode_paper<MT, C, MODE >= 2>(T, valid, x, s, t, [&](int l, const float* h, const int (&node)[8], auto& last) {
 #pragma unroll
-        for (int c = 0; c < C; c += 4) htile_put4<MT>(htile, KB0, lane, l * C + c, &h[c]);
+        for (int c = 0; c < C; c += 4) input4(l * C + c, &h[c]);
         if (keep) {
 #pragma unroll
           for (int d = 0; d < 8; ++d) idx_out[(l * 8 + d) * n_idx + q] = node[d];  // coalesced across lanes
@@ -86,7 +144,7 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
     } else {
       encode_pipelined<MT, C>(T, valid, x, s, t, [&](int l, const float* h, int node, auto& last) {
 #pragma unroll
-        for (int c = 0; c < C; c += 4) htile_put4<MT>(htile, KB0, lane, l * C + c, &h[c]);
+        for (int c = 0; c < C; c += 4) input4(l * C + c, &h[c]);
         if (keep) {
           idx_out[l * n_idx + q] = node;  // level-major: coalesced across lanes
           if constexpr (sizeof(MT) == 2)
@@ -101,7 +159,7 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
     for (int k = 0; k < M.E; k += 4) {
       float g4[4] = {0.f, 0.f, 0.f, 0.f};
       if (valid) load_attr4(src, q, k, g4);
-      htile_put4<MT>(htile, KB0, lane, M.K0 - M.E + k, g4);
+      input4(M.K0 - M.E + k, g4);
       if (sizeof(MT) == 2 && keep && brows) {
         v4 v;
 #pragma unroll
@@ -109,12 +167,25 @@ __global__ __launch_bounds__(512) void query_kernel(const TreeArgs T, const MlpA
         *reinterpret_cast<v4*>(brows + (((M.K0 - M.E + k) >> 2) * n_idx + q) * 4) = v;
       }
     }
+    if constexpr (STREAM) {  // the rest of the last chunk
+      const float z[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int k = M.K0; k & 31; k += 4) input4(k, z);
+    }
     wave_lds_sync();
 #pragma unroll
     for (int t0 = 0; t0 < 4; t0 += NT) {
       f32x4 out[NT];
-      mlp_forward_tiles<MT, H, NT, 0>(
-          M, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<MT>(htile, KB0, t0 + t, kb, lane); }, out);
+      if constexpr (STREAM) {
+        f32x4 acc[MH][NT];
+#pragma unroll
+        for (int m = 0; m < MH; ++m)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[m][t] = acc0[m][t0 + t];
+        mlp_rest<MT, H, NT>(M, W, bias, lane, acc, out);
+      } else {
+        mlp_forward_tiles<MT, H, NT, 0>(
+            M, W, bias, KB0, lane, [&](int kb, int t) { return htile_get<MT>(htile, KB0, t0 + t, kb, lane); }, out);
+      }
       store_rgb<NT>(out, tile * 64 + 16 * t0, Q, lane, rgb);
     }
     wave_lds_sync();
@@ -133,24 +204,35 @@ static void tile_launch_shape_plain(const MlpArgs& M, int64_t Q, int& waves, siz
   grid = tile_grid((Q + 63) / 64, lds);
 }
 
-// Workgroup shape for the tile kernels: up to 8 waves, each with a 64-query
+// Workgroup shape for the tile kernels: up to query_waves, each with a 64-query
 // activation tile, plus the packed weights when they fit next to them.
 template <class MT>
-static void tile_launch_shape(const MlpArgs& M, int64_t Q, bool& wlds, int& waves, size_t& lds, int& grid) {
-  const int KB0 = (M.K0 + 31) / 32;
+static void tile_launch_shape(const MlpArgs& M, int mode, int64_t Q, bool& wlds, int& waves, size_t& lds, int& grid) {
+  const int KB0 = query_streams(M.H, true) ? 1 : (M.K0 + 31) / 32;
   const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
   const size_t wbytes = (size_t)packed_weight_elems<MT>(M.n_layers, M.K0, M.H) * sizeof(MT);
   const size_t bb = bias_bytes(M);
   const size_t cap = (size_t)max_lds() - bb;
-  waves = 8;
+  waves = query_waves<MT>(M.H, true, mode);
   wlds = true;
   while (waves > 4 && wbytes + waves * tile_bytes > cap) --waves;
   if (wlds && wbytes + waves * tile_bytes > cap) wlds = false;
   if (!wlds) {
-    waves = 8;
-    while (waves > 1 && waves * tile_bytes > cap) --waves;
+    tile_launch_shape_plain<MT>(M, Q, waves, lds, grid);
+    return;
   }
-  lds = bb + (wlds ? wbytes : 0) + waves * tile_bytes;
+  // more than eight waves: the number that wastes least of the last round of
+  // a CU's tiles (a CU with 64 tiles has eight full rounds of 8, but 5 1/3 of
+  // 12: 2^20 queries take 343 us with 8 and 384 with 12; with 57 tiles, eight
+  // rounds of 8 or five of 12, 295 and 282), the larger of equals
+  if (waves > 8) {
+    const int64_t n = ((Q + 63) / 64 + device_cus() - 1) / device_cus();
+    int best = 8;
+    for (int w = 9; w <= waves; ++w)
+      if ((n + w - 1) / w * w <= (n + best - 1) / best * best) best = w;
+    waves = best;
+  }
+  lds = bb + wbytes + waves * tile_bytes;
   grid = tile_grid((Q + 63) / 64, lds);
 }
 
@@ -161,7 +243,7 @@ static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const Quer
   bool wlds;
   int waves, grid;
   size_t lds;
-  tile_launch_shape<MT>(M, Q, wlds, waves, lds, grid);
+  tile_launch_shape<MT>(M, MODE, Q, wlds, waves, lds, grid);
   if (wlds && MODE >= 2) {  // the shifted variants: keep one of each
     wlds = false;
     tile_launch_shape_plain<MT>(M, Q, waves, lds, grid);

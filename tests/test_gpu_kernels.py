@@ -232,3 +232,26 @@ def test_shifted_residual_query_order(D, B, N):
     moved = {k: (v[p] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
     for name, u, v in zip(("lhs", "rhs", "resid", "idx"), run(bt), run(moved)):
         assert np.array_equal(u[p], v), name
+
+
+@pytest.mark.parametrize("levels,C,n_attr", [(1, 4, 0), (4, 4, 4), (4, 8, 0), (4, 8, 28), (4, 8, 96), (3, 8, 4)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("B", [1, 65, 4099, 150001])
+def test_streamed_query(levels, C, n_attr, dtype, B):
+    """64-wide decoders, whose first layer takes the inputs in chunks of 32 as
+    they are gathered: inputs that end with a chunk, within one and in the
+    surface attributes, up to the most; single queries up to more than eight
+    tiles per compute unit. The encoding followed by the standalone decoder
+    adds the same products in the same order: equal to the bit."""
+    res = (8, 4, 4, 2)[:levels]
+    tree, mlp, _ = tiny_problem(seed=6, D=levels - 1, res=res, C=C, B=2, N=0, n_attr=n_attr, bias_scale=0.1)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, list(res), C, tree.feat, mlp.W, mlp.b, dtype=dtype)
+    g = np.random.default_rng(B)
+    t = lambda *s: torch.from_numpy(g.uniform(0, 1, s).astype(np.float32)).cuda()
+    x, d, attr = t(B, 3), t(B, 3) - 0.5, t(B, n_attr) if n_attr else None
+    print(f"[case] streamed query L={levels} C={C} E={n_attr} {dtype} B={B}", flush=True)
+    rgb = model(x, d, attr) if n_attr else model(x, d)
+    h, _ = binding.encode_query(model.tree, x, d, dtype, feat=model.work_feat)
+    if n_attr:
+        h = torch.cat([h, attr.to(dtype)], 1)
+    assert torch.equal(rgb, binding.mlp_fwd(model.mlp, h.contiguous(), W=model.work_W))
