@@ -1021,7 +1021,8 @@ int oo_adam_step(const oo_adam_config* cfg, const oo_adam_segment* segs, int32_t
     const size_t wa = cfg->work_dtype == OO_F32 ? 16 : 8;
     const bool vec = ((uintptr_t)S.param | (uintptr_t)S.grad | (uintptr_t)S.m | (uintptr_t)S.v) % 16 == 0 &&
                      (uintptr_t)S.work % wa == 0;
-    A.seg[s] = AdamSeg{S.param, S.grad, S.m, S.v, S.work, S.n, S.touched, S.block, vec ? 1 : 0};
+    A.seg[s] = AdamSeg{S.param, S.grad, S.m, S.v, S.work, S.n, S.touched, S.block, vec ? 1 : 0, -1};
+    if (S.block > 0 && (S.block & (S.block - 1)) == 0) A.seg[s].shift = __builtin_ctzll(S.block);
     A.first[s + 1] = A.first[s] + (S.n + 3) / 4;
   }
   A.lr = cfg->lr;

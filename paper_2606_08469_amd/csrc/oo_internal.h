@@ -214,6 +214,7 @@ struct AdamSeg {
   const uint32_t* touched;
   int64_t block;
   int vec;  // every array aligned for one vector of 4 elements per thread
+  int shift;  // block = 1 << shift, or -1
 };
 struct AdamArgs {
   int32_t n_segs;
