@@ -213,12 +213,21 @@ __global__ __launch_bounds__(256) void combine_kernel(const ResidualArgs A, int 
   if (threadIdx.x == 0) partials[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Fixed-order sum of the block partials: loss = sum / (3B).
+// Fixed-order sum of the block partials: loss = sum / (3B). One workgroup, so
+// a chain of latencies: 32,768 partials take 10 us with 16 in flight per
+// thread, 34 one by one.
 __global__ __launch_bounds__(256) void loss_reduce_kernel(const double* __restrict__ partials, int n, int64_t B,
                                                           double* __restrict__ loss) {
   __shared__ double red[256];
   double acc = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) acc += partials[i];
+  constexpr int U = 16;  // partials in flight per thread, added in the plain loop's order
+  for (int i0 = threadIdx.x; i0 < n; i0 += 256 * U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i0 + 256 * u < n ? partials[i0 + 256 * u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += v[u];
+  }
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {

@@ -255,3 +255,33 @@ def test_streamed_query(levels, C, n_attr, dtype, B):
     if n_attr:
         h = torch.cat([h, attr.to(dtype)], 1)
     assert torch.equal(rgb, binding.mlp_fwd(model.mlp, h.contiguous(), W=model.work_W))
+
+
+@pytest.mark.parametrize("B", [1, 1025, 65600, 66000, 200000, 262145])
+def test_residual_query_order(B):
+    """The bucketed order over one chunk of queries, a few, one more than a
+    quarter of the most and all of them: a query's result does not depend on
+    where it is evaluated, so permuting the batch permutes every output and
+    the node indices, bit for bit."""
+    tree, mlp, _ = tiny_problem(seed=8, D=4, res=(8, 8, 4, 4, 2), B=2, N=0)
+    g = np.random.default_rng(12)
+    f32 = lambda *s: g.uniform(-1, 1, s).astype(np.float32)
+    bt = dict(x=0.5 + 0.5 * f32(B, 3), dir=f32(B, 3), n=f32(B, 3), wo=f32(B, 3), albedo=f32(B, 3), rough=f32(B),
+              Le=f32(B, 3), N=0, F0=0.04, loss_kind=0, eps=1e-2, grad_through_rhs=0, target_override=f32(B, 3),
+              wi=None, pdf=None, x2=None, dir2=None)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, tree.res, 4, tree.feat, mlp.W, mlp.b)
+    print(f"[case] residual order B={B}", flush=True)
+
+    def run(batch):
+        dev = binding.device_batch(batch)
+        ws = model.workspace(dev)
+        out = binding.residual_fwd(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)
+        idx = binding.residual_node_indices(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)
+        return [to_np(t) for t in (out[0], out[2], idx)]
+
+    p = g.permutation(B)
+    moved = {k: (v[p] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
+    base = run(bt)
+    for name, u, v in zip(("lhs", "resid", "idx"), base, run(moved)):
+        assert np.array_equal(u[p], v), name
+    assert np.array_equal(base[2], oracle.descend(tree, bt["x"]))
