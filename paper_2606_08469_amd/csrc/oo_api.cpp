@@ -21,7 +21,7 @@ namespace {
 
 thread_local char g_err[512] = "";
 
-// The backward runs in up to kMaxChunks chunks of at least kChunkQueries
+// The FP32 backward runs in up to kMaxChunks chunks of at least kChunkQueries
 // sorted positions; the feature scatter of chunk c runs on a second stream
 // while the backward kernel works on chunk c + 1 (the scatter is bound by
 // the memory-side atomic units, the backward by latency, so they overlap).
@@ -821,7 +821,11 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
   const float2* uv = reinterpret_cast<const float2*>(ws + w.uv);
   const float4* pos = reinterpret_cast<const float4*>(ws + w.pos);
   float* dh = reinterpret_cast<float*>(ws + w.dh);
-  const int nc = bwd_chunks(Qb);
+  GA.coarse = coarse_levels(T, GA, Qb);
+  // (the 16-bit backward fills a CU's registers and LDS: beside it the scatter
+  // gains nothing, and one launch of each takes 3458 us of a step of 2^20
+  // points x 9 where four of each on two streams took 3494)
+  const int nc = runs_bwd16(M, mlp->dtype) ? 1 : bwd_chunks(Qb);
   const int64_t chunk = ((Qb + nc - 1) / nc + 63) / 64 * 64;  // whole 64-query tiles
   {
     std::lock_guard<std::mutex> lk(g_side_m);
@@ -861,6 +865,11 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
                            ss);
       }
       if (e != hipSuccess) return hip_status(e, "scatter launch");
+    }
+    if (GA.coarse) {  // beside the last chunk's scatter
+      ProfScope ps(OO_PROF_SCATTER, stream);
+      e = launch_scatter_coarse(T, Qb, nidx, uv, dh, post_scale, GA, stream);
+      if (e != hipSuccess) return hip_status(e, "coarse scatter launch");
     }
     if (side) {  // the caller's stream continues after the last scatter
       if ((e = hipEventRecord(side->ev[kMaxChunks], side->s)) != hipSuccess) return hip_status(e, "event record");

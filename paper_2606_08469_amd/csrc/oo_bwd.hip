@@ -249,9 +249,9 @@ __global__ __launch_bounds__(64 * bwd_waves<MT>()) void bwd_kernel(const TreeArg
   constexpr int MH = H / 16, MH2 = MH / kMSplit;
   constexpr int U0 = (MH * 8 + NW - 1) / NW, UH = (MH * MH + NW - 1) / NW;
   constexpr int UO = (MH + NW - 1) / NW;
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: scalar branches
-  const int nt = wave & 3, mh = wave >> 2, col = 16 * nt + r16;  // mh = 0 with 4 waves
+  const int nt = wave & 3, mh = wave >> 2;  // mh = 0 with 4 waves
   const int K0 = M.K0, NL = M.n_layers, L = T.L, LC = L * C;
   const BwdLayout lay = bwd_layout(K0, H, NL, L, (int)sizeof(MT));
   const int KB0 = lay.KB0, R0 = lay.R0;
@@ -806,7 +806,8 @@ hipError_t launch_bwd(const TreeArgs& T, oo_dtype td, const MlpArgs& M, oo_dtype
 // share one chunk and a 2x2 map (the finest levels) takes two chunks per
 // query. This request rate, not bandwidth, bounds the step; privatising
 // coarse-level maps in LDS does not pay here, because LDS float atomics
-// retire about one lane per clock per CU. Each lane adds
+// retire about one lane per three clocks per CU (integer ones twelve lanes
+// per clock, which is why scatter_coarse_kernel sorts instead). Each lane adds
 // w_tap * dh[q][l C + c] * post_scale with a hardware FP32 atomic. Node
 // indices and octahedral coordinates come from the forward ([L][Q] and [Q]);
 // indices are range-checked and coordinates clamped, and the taps are
@@ -818,6 +819,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const TreeArgs T, int64_t 
                                                       float post_scale, const GradArgs G) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x, n = Q * 4 * C;
   for (int l = 0; l < T.L; ++l) {
+    if ((G.coarse >> l) & 1u) continue;
     const int R = T.res[l];
     float* const pad = G.pad[l];
     for (int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; gid < n; gid += stride) {
@@ -851,6 +853,195 @@ __global__ __launch_bounds__(256) void scatter_kernel(const TreeArgs T, int64_t 
       }
     }
   }
+}
+
+// The same for the levels in G.coarse, where many queries share a footprint
+// (the 2x2 texels around a lookup): a workgroup takes a run of consecutive
+// sorted positions, which lie in a few nodes of such a level, brings them in
+// footprint order by a counting sort in LDS, and adds up the four taps' sums
+// of a footprint in registers before its two rows go out as one request
+// each. Footprints past the counters' end stay in any order at the run's end:
+// an accumulator goes out whenever the next query has another footprint, so
+// the order matters for speed only. 16 lanes per query (tap column,
+// channel), 64 groups, each with an equal share of the run and eight queries'
+// loads in flight. Bound by the atomic units' request rate (20 billion
+// 64-byte requests a second) and the gathers of dh: four levels of 2^20
+// queries take 215 us here, and with the levels left 1026 us in place of 1300
+// in scatter_kernel alone.
+//
+// A level qualifies (coarse_levels) where two queries or more share a
+// footprint on average, over all its nodes and within a run over one node;
+// fewer would cost the same requests and the sort on top. Below kCoarseMin
+// queries the launch costs more than it saves: steps on maps of 32^2 texels
+// and fewer take 277 us with it and 265 without for 66,000 points, 355 and
+// 372 for 131,072, 524 and 608 for 262,144.
+constexpr int64_t kCoarseMin = 1 << 17;
+constexpr int kCoarseThreads = 1024;
+constexpr int kCoarseCap = 8192;                  // footprints with a counter
+constexpr int kCoarsePer = 16;                    // positions per thread
+constexpr int kCoarseRun = kCoarseThreads * kCoarsePer;
+constexpr int kCoarseRunMin = 4 * kCoarseThreads;
+struct CoarseArgs {
+  int n, run;
+  int level[kMaxLevels];
+};
+
+__global__ __launch_bounds__(kCoarseThreads) void scatter_coarse_kernel(const TreeArgs T, int64_t Q,
+                                                                        const int32_t* __restrict__ nidx,
+                                                                        const float2* __restrict__ uv,
+                                                                        const float* __restrict__ dh, float post_scale,
+                                                                        const GradArgs G, const CoarseArgs A) {
+  constexpr int C = 8, W = kCoarseThreads / 64, U = 8;
+  __shared__ int cnt[kCoarseCap], wsum[W], id_min, n_over;
+  __shared__ uint16_t list[kCoarseRun];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l = A.level[blockIdx.y], R = T.res[l], cells = (R + 1) * (R + 1);
+  const int64_t q0 = (int64_t)blockIdx.x * A.run;
+  const int n = (int)(Q - q0 < A.run ? Q - q0 : A.run);
+  const int32_t* const ids = nidx + (int64_t)l * Q + q0;
+  if (tid == 0) {
+    id_min = INT32_MAX;
+    n_over = 0;
+  }
+#pragma unroll
+  for (int i = 0; i < kCoarseCap / kCoarseThreads; ++i) cnt[tid + i * kCoarseThreads] = 0;
+  __syncthreads();
+  // column and row (in [-1, R - 1], as in scatter_kernel) of a lookup's footprint
+  auto footprint = [&](const float2& p, float& fu, float& fv, int& i0, int& j0) {
+    const float s = fminf(fmaxf(p.x, 0.0f), 1.0f), t = fminf(fmaxf(p.y, 0.0f), 1.0f);
+    const float pu = s * (float)R - 0.5f, pv = t * (float)R - 0.5f;
+    const float fi = floorf(pu), fj = floorf(pv);
+    fu = pu - fi;
+    fv = pv - fj;
+    i0 = (int)fi;
+    j0 = (int)fj;
+  };
+  int id[kCoarsePer], least = INT32_MAX;
+#pragma unroll
+  for (int k = 0; k < kCoarsePer; ++k) {
+    const int i = k * kCoarseThreads + tid;
+    id[k] = i < n ? ids[i] : -1;
+    if (id[k] < T.off[l] || id[k] >= T.off[l + 1]) id[k] = -1;
+    if (id[k] >= 0) least = min(least, id[k]);
+  }
+  for (int off = 32; off >= 1; off >>= 1) least = min(least, __shfl_xor(least, off));
+  if (lane == 0) atomicMin(&id_min, least);
+  __syncthreads();
+  int key[kCoarsePer], slot[kCoarsePer];
+#pragma unroll
+  for (int k = 0; k < kCoarsePer; ++k) {
+    key[k] = -1;
+    if (id[k] < 0) continue;
+    float fu, fv;
+    int i0, j0;
+    footprint(uv[q0 + k * kCoarseThreads + tid], fu, fv, i0, j0);
+    const int64_t at = (int64_t)(id[k] - id_min) * cells + (j0 + 1) * (R + 1) + (i0 + 1);
+    key[k] = at < kCoarseCap ? (int)at : kCoarseCap;
+    slot[k] = atomicAdd(key[k] < kCoarseCap ? &cnt[key[k]] : &n_over, 1);
+  }
+  __syncthreads();
+  constexpr int per = kCoarseCap / kCoarseThreads;
+  int v[per], s = 0;
+#pragma unroll
+  for (int i = 0; i < per; ++i) s += v[i] = cnt[tid * per + i];
+  int run = s;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int t = __shfl_up(run, off);
+    if (lane >= off) run += t;
+  }
+  if (lane == 63) wsum[wave] = run;
+  __syncthreads();
+  run -= s;
+  int counted = 0;
+  for (int w = 0; w < W; ++w) {
+    if (w == wave) run += counted;
+    counted += wsum[w];
+  }
+#pragma unroll
+  for (int i = 0; i < per; ++i) {
+    cnt[tid * per + i] = run;
+    run += v[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kCoarsePer; ++k)
+    if (key[k] >= 0)
+      list[(key[k] < kCoarseCap ? cnt[key[k]] : counted) + slot[k]] = (uint16_t)(k * kCoarseThreads + tid);
+  const int total = counted + n_over;  // (n_over is complete since the barrier after the counting)
+  __syncthreads();
+  const int g = tid >> 4, a = (tid >> 3) & 1, c = tid & 7;
+  const int share = (total + kCoarseThreads / 16 - 1) / (kCoarseThreads / 16);
+  const int lo = g * share, hi = min(lo + share, total);
+  float* const pad = G.pad[l];
+  const int64_t LC = (int64_t)T.L * C;
+  int64_t open = -1;
+  float acc0 = 0.0f, acc1 = 0.0f;
+  auto flush = [&] {
+    if (open < 0) return;
+    unsafeAtomicAdd(pad + (open + a) * C + c, acc0);
+    unsafeAtomicAdd(pad + (open + 2 * (R + 1) + a) * C + c, acc1);
+  };
+  for (int e0 = lo; e0 < hi; e0 += U) {
+    int node[U];
+    float2 p[U];
+    float d[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = list[min(e0 + u, hi - 1)];
+      node[u] = ids[i];
+      p[u] = uv[q0 + i];
+      d[u] = dh[(q0 + i) * LC + l * C + c];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (e0 + u >= hi) break;
+      float fu, fv;
+      int i0, j0;
+      footprint(p[u], fu, fv, i0, j0);
+      const int64_t at = ((((int64_t)node[u] - T.off[l]) * (R + 2) + (j0 + 1)) * (R + 1) + (i0 + 1)) * 2;
+      if (at != open) {
+        flush();
+        open = at;
+        acc0 = acc1 = 0.0f;
+      }
+      const float gv = d[u] * post_scale, wa = a ? fu : 1.0f - fu;
+      acc0 += wa * (1.0f - fv) * gv;
+      acc1 += wa * fv * gv;
+    }
+  }
+  flush();
+}
+
+// Positions per workgroup: as many as give every CU one workgroup.
+static int coarse_run(const TreeArgs& T, const GradArgs& G, int64_t Q) {
+  int padded = 0;
+  for (int l = 0; l < T.L; ++l) padded += G.pad[l] != nullptr;
+  const int64_t run = (Q * padded / cu_count() + kCoarseThreads - 1) / kCoarseThreads * kCoarseThreads;
+  return (int)(run < kCoarseRunMin ? kCoarseRunMin : (run > kCoarseRun ? kCoarseRun : run));
+}
+
+uint32_t coarse_levels(const TreeArgs& T, const GradArgs& G, int64_t Q) {
+  uint32_t m = 0;
+  if (T.C != 8 || Q < kCoarseMin) return m;
+  const int run = coarse_run(T, G, Q);
+  for (int l = 0; l < T.L; ++l) {
+    const int64_t cells = (int64_t)(T.res[l] + 1) * (T.res[l] + 1), nodes = T.off[l + 1] - T.off[l];
+    if (G.pad[l] && cells <= kCoarseCap && run >= 2 * cells && Q >= 2 * nodes * cells) m |= 1u << l;
+  }
+  return m;
+}
+
+hipError_t launch_scatter_coarse(const TreeArgs& T, int64_t Q, const int32_t* nidx, const float2* uv, const float* dh,
+                                 float post_scale, const GradArgs& G, hipStream_t st) {
+  CoarseArgs A;
+  A.n = 0;
+  A.run = coarse_run(T, G, Q);
+  for (int l = 0; l < T.L; ++l)
+    if ((G.coarse >> l) & 1u) A.level[A.n++] = l;
+  if (A.n == 0 || Q == 0) return hipSuccess;
+  hipLaunchKernelGGL(scatter_coarse_kernel, dim3((unsigned)((Q + A.run - 1) / A.run), A.n), dim3(kCoarseThreads), 0, st,
+                     T, Q, nidx, uv, dh, post_scale, G, A);
+  return hipGetLastError();
 }
 
 // Feature-gradient scatter of the paper's scheme: 8 C lanes per (query,

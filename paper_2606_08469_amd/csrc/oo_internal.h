@@ -26,6 +26,7 @@ struct ResidualArgs {
 struct GradArgs {
   float* dfeat[kMaxLevels];
   float* pad[kMaxLevels];
+  uint32_t coarse = 0;  // levels that launch_scatter_coarse takes instead of launch_scatter
 };
 
 // Floats of a level's pair buffer: per node, R + 2 rows (unwrapped rows -1
@@ -172,6 +173,11 @@ struct ShiftArgs {
 hipError_t launch_scatter(const TreeArgs& T, oo_dtype td, int64_t Q, const int32_t* nidx, int64_t ldn,
                           const float2* uv, const float4* pos, const float* dh, float post_scale, const GradArgs& G,
                           const ShiftArgs& S, hipStream_t st);
+// The levels with pair buffers on which many of the Q backward queries share
+// a footprint, and their scatter, over all queries in one launch.
+uint32_t coarse_levels(const TreeArgs& T, const GradArgs& G, int64_t Q);
+hipError_t launch_scatter_coarse(const TreeArgs& T, int64_t Q, const int32_t* nidx, const float2* uv, const float* dh,
+                                 float post_scale, const GradArgs& G, hipStream_t st);
 // Disparity predictor backward over the Q sorted backward queries (x, dir
 // from src; dd[q] = dLoss/d disparity), at most `cap` queries per pass
 // through the row buffer `rows` (disparity_rows_floats(cap) floats):

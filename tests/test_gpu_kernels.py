@@ -285,3 +285,41 @@ def test_residual_query_order(B):
     for name, u, v in zip(("lhs", "resid", "idx"), base, run(moved)):
         assert np.array_equal(u[p], v), name
     assert np.array_equal(base[2], oracle.descend(tree, bt["x"]))
+
+
+@pytest.mark.parametrize("res,B,spread", [((8, 8, 8), 131071, 1.0), ((8, 8, 8), 131072, 1.0), ((8, 16, 8, 8), 140001, 0.1),
+                                          ((32, 32, 32), 150001, 0.03), ((8, 32, 16, 2), 262145, 0.3)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_coarse_scatter(res, B, spread, dtype):
+    """Feature gradients of a batch large enough for the scatter that adds up
+    shared footprints first, against the same points in batches too small for
+    it (whose gradients add up, weighted by their points): the least number of
+    points and one less, nodes that few points share, runs over more
+    footprints than have counters, several runs per level. The same products
+    in another order: 2^-24 times the terms of a sum, at most 2^16 a texel
+    and mostly of both signs, so 2^-24 * 2^8 * 4 of the gradient's norm."""
+    tree, mlp, _ = tiny_problem(seed=9, D=len(res) - 1, res=res, C=8, B=2, N=0)
+    g = np.random.default_rng(13)
+    u = lambda *s: g.uniform(0, 1, s).astype(np.float32)
+    x = u(B, 3) * np.where(u(B, 1) < spread, 1.0, 0.2).astype(np.float32)
+    bt = dict(x=x, dir=u(B, 3) - np.float32(0.5), n=u(B, 3), wo=u(B, 3), albedo=u(B, 3), rough=u(B), Le=u(B, 3), N=0,
+              F0=0.04, loss_kind=0, eps=1e-2, grad_through_rhs=0, target_override=u(B, 3), wi=None, pdf=None, x2=None,
+              dir2=None)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, list(res), 8, tree.feat, mlp.W, mlp.b, dtype=dtype)
+    print(f"[case] coarse scatter res={res} B={B} spread={spread} {dtype}", flush=True)
+
+    def grads(lo, hi):
+        part = {k: (v[lo:hi] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
+        for f in model.feat:
+            f.grad = None
+        model.residual(binding.device_batch(part)).backward()
+        return [f.grad.double() * (hi - lo) for f in model.feat]
+
+    whole = grads(0, B)
+    want = [torch.zeros_like(w) for w in whole]
+    for lo in range(0, B, 30000):
+        for w, p in zip(want, grads(lo, min(lo + 30000, B))):
+            w += p
+    for l, (a, b) in enumerate(zip(whole, want)):
+        assert b.norm() > 0
+        assert float((a - b).norm() / b.norm()) <= 2.0 ** -14, l
