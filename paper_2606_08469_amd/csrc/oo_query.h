@@ -21,7 +21,7 @@ namespace oo {
 // MODE as for encode_kernel; with the shift rgb[3 q] holds query q's
 // disparity when the kernel starts (the wave that reads it writes the
 // radiance there).
-// Streaming (64-wide layers with the weights in LDS): the first layer takes
+// Streaming (64-wide layers with the weights in LDS, node scheme): the first layer takes
 // the inputs chunk by chunk while the gathers of the next levels are in
 // flight, so a wave's tile holds one chunk of 32 and the LDS holds more waves:
 // gathers, conversions and MFMAs of different waves overlap. 1280x720 queries,
@@ -29,18 +29,19 @@ namespace oo {
 // one, 309 -> 282 us; FP16 four in place of two, 72 -> 68 us (144 registers,
 // which allow three only, 73 us). At width 128 the sums of the first layer
 // alone take 128 registers, which leaves the two waves that whole tiles
-// allow too.
-constexpr bool query_streams(int H, bool wlds) { return H == 64 && wlds; }
+// allow too; the paper scheme's encode takes so many itself that streaming
+// spills them (1280x720 queries in FP16: 0.56 ms, whole tiles 0.28).
+constexpr bool query_streams(int H, bool wlds, int mode) { return H == 64 && wlds && mode == 0; }
 // Waves per workgroup: FP32 takes one workgroup per CU, up to twelve waves
 // where the registers (168) do without scratch memory to speak of, 16-bit two
 // of eight waves (128 registers).
 template <class MT>
 constexpr int query_waves(int H, bool wlds, int mode) {
-  return query_streams(H, wlds) && mode == 0 && sizeof(MT) == 4 ? 12 : 8;
+  return query_streams(H, wlds, mode) && sizeof(MT) == 4 ? 12 : 8;
 }
 template <class MT>
 constexpr int query_waves_per_simd(int H, bool wlds, int mode) {
-  return query_waves<MT>(H, wlds, mode) / 4 * (query_streams(H, wlds) && sizeof(MT) == 2 ? 2 : 1);
+  return query_waves<MT>(H, wlds, mode) / 4 * (query_streams(H, wlds, mode) && sizeof(MT) == 2 ? 2 : 1);
 }
 
 // KEEP: the queries of this launch are the backward's (q < n_idx). The
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(64 * query_waves<MT>(H, WLDS, MODE))
   constexpr int NT = sizeof(MT) == 2 && WLDS && H == 64 ? 4 : 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
   const int KB0 = (M.K0 + 31) / 32;
-  constexpr bool STREAM = query_streams(H, WLDS);
+  constexpr bool STREAM = query_streams(H, WLDS, MODE);
   constexpr int MH = H / 16;
   const int KBT = STREAM ? 1 : KB0;  // chunks the wave's tile holds
   const int wl_elems = WLDS ? packed_weight_elems<MT>(M.n_layers, M.K0, M.H) : 0;
@@ -208,7 +209,7 @@ static void tile_launch_shape_plain(const MlpArgs& M, int64_t Q, int& waves, siz
 // activation tile, plus the packed weights when they fit next to them.
 template <class MT>
 static void tile_launch_shape(const MlpArgs& M, int mode, int64_t Q, bool& wlds, int& waves, size_t& lds, int& grid) {
-  const int KB0 = query_streams(M.H, true) ? 1 : (M.K0 + 31) / 32;
+  const int KB0 = query_streams(M.H, true, mode) ? 1 : (M.K0 + 31) / 32;
   const size_t tile_bytes = (size_t)4 * KB0 * kWave * 8 * sizeof(MT);
   const size_t wbytes = (size_t)packed_weight_elems<MT>(M.n_layers, M.K0, M.H) * sizeof(MT);
   const size_t bb = bias_bytes(M);
