@@ -181,11 +181,14 @@ def main():
     # scatter requests to the atomic units: per LHS query and present level,
     # two footprint rows of 2 texels, each one 64-byte chunk when it starts on
     # an even texel and two otherwise (1.5 on average); a 2x2 map is 2 chunks,
-    # and so is a level whose gradients go through the library's pair buffers
+    # and so is a level whose gradients go through the library's pair buffers;
+    # levels whose shared footprints are summed before they go out send fewer
+    # and are left out (their launch counts in the time)
     per_level = (idx[:B] >= 0).sum(0).to(torch.float64).cpu().numpy()
     paired = pair_buffered_levels(cfg, np.diff(lo))
+    merged = merged_levels(cfg, np.diff(lo), paired, B)
     atomic_req = float(sum(n * (2.0 if (r == 2 or l in paired) else 3.0)
-                           for l, (n, r) in enumerate(zip(per_level, cfg.res))))
+                           for l, (n, r) in enumerate(zip(per_level, cfg.res)) if l not in merged))
     del xq, dq, idx, present
     kern = kernel_rooflines(cfg, B, Q, lv_all, lv_lhs, per_kernel)
     if "scatter" in kern:
@@ -194,10 +197,8 @@ def main():
         rate = req / (k["ms_per_launch"] * 1e-3) / 1e9
         k.update(atomic_requests=int(req), atomic_Greq_s=round(rate, 2), atomic_ceiling_Greq_s=ATOMIC_GREQ_S,
                  frac_of_atomic_ceiling=round(rate / ATOMIC_GREQ_S, 4))
-    # the dominant kernel: most launch time per step on the caller's stream
-    # (the scatter runs beside the decoder backward on a second stream, so
-    # it is reported in `kernels` but not chosen here)
-    dom = max((k for k in kern if k != "scatter"), key=lambda k: kern[k]["ms_per_step"])
+    # the dominant kernel: most launch time per step
+    dom = max(kern, key=lambda k: kern[k]["ms_per_step"])
     roof = {"kernel": dom, **kern[dom], "kernels": kern,
             "traffic_source": ("profiles/traffic_train_step_cfg5.txt" if kern[dom]["traffic"] is not None
                                else "no counter summary for the current kernels")}
@@ -485,8 +486,7 @@ MFMA_F16_PEAK_TFS = 2500.0  # MI355X dense FP16 matrix cores
 def kernel_rooflines(cfg, B, Q, lv_all, lv_lhs, per_kernel):
     """Algorithmic bytes and FLOPs per launch of the three dominant kernels of
     the step, against their launch times measured in the timed region (the
-    backward and the scatter run in several launches per step, each over its
-    share of the queries).
+    scatter's coarse levels are a launch of their own).
 
     Algorithmic bytes are the method's own work (lv = sum over queries of
     the levels that have a node, FP16 texels):
@@ -498,26 +498,25 @@ def kernel_rooflines(cfg, B, Q, lv_all, lv_lhs, per_kernel):
        of 4 B.
     Traffic that only this implementation's split causes is listed apart as
     implementation_bytes: the bucketed order (4 B per query) and the node
-    indices and octahedral coordinates the forward keeps for the backward
-    (4 B per level + 8 B per LHS query); in the backward those indices and
-    coordinates, the order entry, and the FP32 dh it hands to the scatter
-    (K0 x 4 B per LHS query); in the scatter the dh, node index and
-    coordinates it reads back."""
+    indices, octahedral coordinates and decoder inputs the forward keeps for
+    the backward (4 B per level + 8 B + K0 x 2 B per LHS query); in the backward those
+    inputs and the FP32 dh it hands to the scatter (K0 x 4 B per LHS query);
+    in the scatter the dh, node index and coordinates it reads back."""
     C, L, K0 = cfg.C, len(cfg.res), cfg.mlp[0]
     H = cfg.mlp[1]
     mlp_flop = 2 * (K0 * H + (len(cfg.mlp) - 3) * H * H + H * 3)
     gather = 4 * C * 2 + 4
     out = {}
     spec = {
-        "query": (lv_all * gather + Q * (24 + 12), Q * 4 + B * (L * 4 + 8), Q * mlp_flop),
-        "backward": (lv_lhs * gather + B * (24 + 12 + 12), B * (8 + 4 + K0 * 4), B * 3 * mlp_flop),
+        "query": (lv_all * gather + Q * (24 + 12), Q * 4 + B * (L * 4 + 8 + K0 * 2), Q * mlp_flop),
+        "backward": (lv_lhs * gather + B * (24 + 12 + 12), B * (K0 * 2 + K0 * 4), B * 3 * mlp_flop),
         "scatter": (lv_lhs * 4 * C * 4, lv_lhs * (C * 4 + 4) + B * 8, 0),
     }
     counters = counter_traffic()
     for k, (nbytes, impl, flop) in spec.items():
         if k not in per_kernel:
             continue
-        # the backward runs in chunks: per-launch work is the step's share
+        # several launches per step: per-launch work is the step's share
         per_step = per_kernel[k][1]
         nbytes, impl, flop = nbytes / per_step, impl / per_step, flop / per_step
         t = per_kernel[k][0] * 1e-3
@@ -568,6 +567,18 @@ def pair_buffered_levels(cfg, nodes_per_level):
     return out
 
 
+def merged_levels(cfg, nodes_per_level, paired, B):
+    """Pair-buffered levels on which the library sums the footprints that
+    several of the B points share before the atomic adds: from 2^17 points
+    on, where a level has at least two points per footprint, over all its
+    nodes and within the run of points a workgroup takes over one."""
+    if B < 1 << 17:
+        return set()
+    run = min(max(-(-B * len(paired) // (256 * 1024)) * 1024, 4096), 16384)
+    cells = [(r + 1) ** 2 for r in cfg.res]
+    return {l for l in paired if run >= 2 * cells[l] and B >= 2 * int(nodes_per_level[l]) * cells[l]}
+
+
 def source_digest():
     """SHA-256 over the library sources: a stored counter reading is only
     used while the kernels it measured are unchanged."""
@@ -578,7 +589,8 @@ def source_digest():
         if f.endswith((".hip", ".h", ".cpp")):
             h.update(f.encode())
             h.update(open(os.path.join(csrc, f), "rb").read())
-    h.update(open(os.path.join(ROOT, "include", "octaoctree.h"), "rb").read())
+    for f in sorted(os.listdir(os.path.join(ROOT, "include"))):
+        h.update(open(os.path.join(ROOT, "include", f), "rb").read())
     return h.hexdigest()
 
 

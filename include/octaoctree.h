@@ -245,21 +245,6 @@ int oo_query_fwd(const oo_tree* tree, const oo_mlp* mlp, const float* x, const f
                  int64_t B, float* rgb_out, hipStream_t stream);
 
 /*
- * oo_query_fwd with a workspace (device memory of the caller, free again
- * when the work on `stream` has passed the call). With a disparity predictor
- * the queries then run as three kernels (predictor, shifted encode into
- * decoder input rows, decoder), several times faster than the fused one;
- * trees without a predictor run the fused kernel and need no workspace. The
- * results are those of oo_query_fwd.
- *  - oo_query_workspace_bytes: the size this needs for B queries (0 without
- *    a predictor; bounded, since large batches run in passes).
- *  - workspace_bytes smaller than that: OO_EINVAL, before any launch.
- */
-int oo_query_workspace_bytes(const oo_tree* tree, const oo_mlp* mlp, int64_t B, size_t* bytes);
-int oo_query_fwd_ws(const oo_tree* tree, const oo_mlp* mlp, const float* x, const float* dir, const float* attr,
-                    int64_t B, float* rgb_out, void* workspace, size_t workspace_bytes, hipStream_t stream);
-
-/*
  * One batch of the neural-radiosity residual (Sec. 3.2 Monte-Carlo RHS;
  * Sec. 3.6 loss). All pointers are device pointers.
  *  - B: number of LHS points. N: secondary samples per point, N >= 0.
@@ -515,4 +500,6 @@ const char* oo_last_error(void);
 #ifdef __cplusplus
 }
 #endif
+
+#include "octaoctree_render.h" /* oo_query_fwd with a caller workspace */
 #endif /* OCTAOCTREE_H */
