@@ -613,7 +613,7 @@ class OctaOctree(torch.nn.Module):
 
 class RadiosityResidual(torch.autograd.Function):
     """Neural-radiosity residual loss. Forward evaluates LHS and RHS queries
-    and the FP64 loss; backward recomputes the LHS encoding, runs the decoder
+    and the FP64 loss; backward recomputes the LHS decoder, runs the decoder
     backward on matrix cores and scatters feature gradients with FP32
     atomics. Gradients w.r.t. the 16-bit working copies are returned for the
     FP32 masters.
