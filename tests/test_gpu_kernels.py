@@ -323,3 +323,21 @@ def test_coarse_scatter(res, B, spread, dtype):
     for l, (a, b) in enumerate(zip(whole, want)):
         assert b.norm() > 0
         assert float((a - b).norm() / b.norm()) <= 2.0 ** -14, l
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("B", [1, 16384, 16385])
+def test_residual_query_launches(dtype, B):
+    """Backward's and secondary queries in one launch (up to 2^15 queries)
+    and in two: what a query gives does not depend on it. LHS radiance equal
+    to the plain query's to the bit, node indices to the oracle's."""
+    tree, mlp, bt = tiny_problem(seed=10, D=3, res=(8, 4, 4, 2), B=max(B, 2), N=1)
+    bt = {k: (v[:B] if isinstance(v, np.ndarray) else v) for k, v in bt.items()}
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, tree.res, 4, tree.feat, mlp.W, mlp.b, dtype=dtype)
+    dev = binding.device_batch(bt)
+    print(f"[case] residual launches B={B} {dtype}", flush=True)
+    ws = model.workspace(dev)
+    lhs = binding.residual_fwd(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)[0]
+    idx = binding.residual_node_indices(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)
+    assert torch.equal(lhs, model(dev["x"], dev["dir"]))
+    assert np.array_equal(to_np(idx), oracle.descend(tree, bt["x"]))
