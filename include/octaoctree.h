@@ -314,9 +314,12 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
 /*
  * Residual backward. The decoder forward is recomputed from its inputs. With
  * a 16-bit decoder whose backward runs from LDS (every accepted one but four
- * 128-wide hidden layers over more than 96 inputs) the forward keeps those
- * inputs in the workspace, 2 bytes each per query; else the texel gathers are
- * repeated too, from the node index per level that the forward kept.
+ * 128-wide hidden layers over more than 96 inputs) the forward keeps the
+ * level features in the workspace, 2 bytes each per query; else the texel
+ * gathers are repeated too, from the node index per level that the forward
+ * kept. (An FP16 feature is kept as its exact sum of products rounded once;
+ * the forward's decoder reads the FP32 sum rounded to FP16, which can be the
+ * other neighbour.) Surface attributes are read from the batch again.
  *  - workspace: the one the forward of this batch used, unchanged since.
  *    The forward leaves there the bucketed query order and, for every query
  *    the backward processes, its node indices and octahedral coordinates.
@@ -336,12 +339,15 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
  *  - Gradients are for the tables and weights the forward read. In
  *    mixed-precision runs those are the FP16/BF16 working copies, and the
  *    gradient is applied to the FP32 masters.
- *  - Streams: with at least 65,536 backward queries the work runs in up to
- *    four chunks, and the feature scatter of each chunk runs on a second
+ *  - Streams: with at least 65,536 backward queries, an FP32 decoder or a
+ *    16-bit one whose backward does not run from LDS runs in up to four
+ *    chunks, and the feature scatter of each chunk runs on a second
  *    stream that the library creates once per device (default priority),
  *    ordered by events: it starts after that chunk's decoder backward on
  *    `stream`, and `stream` waits for the last scatter before the dW/db
- *    reduction. To the caller the call behaves as work enqueued on `stream`.
+ *    reduction. The other 16-bit decoders run on `stream` alone, in one
+ *    chunk, or in two where the workspace holds dLoss/dh of one at a time.
+ *    To the caller the call behaves as work enqueued on `stream`.
  */
 int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_residual_batch* batch,
                               const float* resid, const float* rhs, const double* grad_loss,

@@ -21,18 +21,36 @@ namespace {
 
 thread_local char g_err[512] = "";
 
-// The FP32 backward runs in up to kMaxChunks chunks of at least kChunkQueries
-// sorted positions; the feature scatter of chunk c runs on a second stream
-// while the backward kernel works on chunk c + 1 (the scatter is bound by
-// the memory-side atomic units, the backward by latency, so they overlap).
+// The backward runs in chunks of at least kChunkQueries sorted positions,
+// whole 64-query tiles each.
+//  - bwd_kernel (FP32, and the 16-bit decoders that oo_bwd16.h has no shape
+//    for): up to kMaxChunks; the feature scatter of chunk c runs on a second
+//    stream while the backward kernel works on chunk c + 1 (the scatter is
+//    bound by the memory-side atomic units, the backward by latency, so they
+//    overlap).
+//  - bwd16_kernel fills a CU's registers and LDS, and beside it the scatter
+//    gains nothing: one chunk (a step of 2^20 points x 9 takes 3420 us; in
+//    four chunks on two streams 3494). Where the kept level features take
+//    more than the forward's scratch gives back (few secondary queries per
+//    backward query), two chunks one after the other, with dh for one of
+//    them: so no batch needs more than features, scratch and dh side by side
+//    less the features. The same step in two such chunks takes 3507 us.
 constexpr int kMaxChunks = 4;
 constexpr int64_t kChunkQueries = 32768;
 
-int bwd_chunks(int64_t Qb) {
-  int64_t n = Qb / kChunkQueries;
-  return (int)(n < 1 ? 1 : (n > kMaxChunks ? kMaxChunks : n));
+struct BwdChunks {
+  bool staged;  // dh holds one chunk at a time
+  int n;
+  int64_t size;
+};
+BwdChunks bwd_chunks(int64_t Qb, bool bwd16, bool tight) {
+  BwdChunks c;
+  const int64_t most = !bwd16 ? kMaxChunks : tight ? 2 : 1, n = Qb / kChunkQueries;
+  c.n = (int)(n < 1 ? 1 : (n > most ? most : n));
+  c.size = ((Qb + c.n - 1) / c.n + 63) / 64 * 64;
+  c.staged = bwd16 && c.n > 1;
+  return c;
 }
-
 
 int fail(int code, const char* fmt, ...) {
   va_list ap;
@@ -308,7 +326,7 @@ size_t query_workspace(int64_t pass, const MlpArgs& M, oo_dtype md, size_t& rows
 
 struct Workspace {
   size_t Lq, lossp, seeds, nidx, uv, pos, dh, wt[OO_MAX_LAYERS], dwp, order, rank, scount, stotal, sstart, gpad, total;
-  size_t brows;  // 16-bit decoders: the inputs of every backward query's decoder, [K0 / 4][Qb][4]
+  size_t brows;  // bwd16_kernel: the level features of every backward query, [L C / 4][Qb][4] in 16 bits
   size_t wdir, dd, gdwp, dsp, drows, hrows;  // the disparity predictor's: lookup directions, dLoss/d
                                              // disparity, parameter partials, disparity of every query,
                                              // backward rows, decoder input rows
@@ -318,6 +336,7 @@ struct Workspace {
   int64_t pad_off[OO_MAX_LEVELS];  // float offset of each level's pair buffer in gpad, or -1
   int64_t pad_total;               // floats in gpad
   int64_t Qb;
+  BwdChunks chunks;
   int grid;
   ParamLayout PL;
 };
@@ -343,6 +362,9 @@ void param_layout(const MlpArgs& M, ParamLayout& PL) {
 // touches them, so the clear and the fold cost little.
 constexpr size_t kPadBudget = size_t(64) << 20;
 
+// Three parts: what the forward keeps for the backward and what only the
+// backward uses; the forward's own scratch, behind the first Qb entries of
+// the bucketed order; and dh, which takes over that scratch.
 Workspace workspace_layout(const MlpArgs& M, oo_dtype md, const oo_residual_batch* b, const oo_tree* tree) {
   Workspace w;
   const int L = tree->n_levels;
@@ -353,73 +375,48 @@ Workspace workspace_layout(const MlpArgs& M, oo_dtype md, const oo_residual_batc
   const int64_t Qb = full ? Qf : B;
   param_layout(M, w.PL);
   w.grid = bwd_grid(M, md, L, Qb);
+  const size_t LC = (size_t)L * tree->C, esz = md == OO_F32 ? 4 : 2;
   size_t o = 0;
-  w.Lq = o;
-  o = align256(o + (size_t)Qf * 3 * sizeof(float));
-  w.lossp = o;
-  o = align256(o + (size_t)(combine_blocks(B, N) + 1) * sizeof(double));
-  w.seeds = o;
-  o = align256(o + (size_t)Qb * 3 * sizeof(float));
+  auto take = [&](size_t bytes) {
+    const size_t at = o;
+    o = align256(o + bytes);
+    return at;
+  };
+  w.seeds = take((size_t)Qb * 3 * sizeof(float));
   w.Qb = Qb;
   const bool paper = tree->interp == OO_INTERP_PAPER;
   w.K = paper ? 8 : 1;
   // node index per level of every backward query, written by the forward,
   // [L][Qb] (paper's scheme: the eight corner cells' nodes, [L][8][Qb])
-  w.nidx = o;
-  o = align256(o + (size_t)Qb * L * w.K * sizeof(int32_t));
-  w.uv = o;  // octahedral coordinates of every backward query, written by the forward, [Qb]
-  o = align256(o + (size_t)Qb * sizeof(float2));
-  w.pos = o;  // paper's scheme: position of every backward query, [Qb]
-  o = align256(o + (paper ? (size_t)Qb * sizeof(float4) : 0));
-  w.brows = o;
-  o = align256(o + (runs_bwd16(M, md) ? (size_t)Qb * M.K0 * 2 : 0));
-  w.dh = o;  // dLoss/dh of every backward query, [Qb][L C] FP32
-  o = align256(o + (size_t)Qb * L * tree->C * sizeof(float));
+  w.nidx = take((size_t)Qb * L * w.K * sizeof(int32_t));
+  // octahedral coordinates of every backward query, written by the forward, [Qb]
+  w.uv = take((size_t)Qb * sizeof(float2));
+  // paper's scheme: position of every backward query, [Qb]
+  w.pos = take(paper ? (size_t)Qb * sizeof(float4) : 0);
+  const bool bwd16 = runs_bwd16(M, md);
+  const size_t rows = bwd16 ? (size_t)Qb * LC * 2 : 0;
+  w.brows = take(rows);
   // with the disparity predictor: unit lookup direction [Qb] float4 and
   // dLoss/d disparity [Qb] of every backward query, and the predictor's
   // parameter partials [ggrid][P]
   const bool shift = paper && tree->disparity;
   w.ggrid = shift ? disparity_bwd_grid(Qb) : 0;
-  w.wdir = o;
-  o = align256(o + (shift ? (size_t)Qb * sizeof(float4) : 0));
-  w.dd = o;
-  o = align256(o + (shift ? (size_t)Qb * sizeof(float) : 0));
-  w.dsp = o;  // [Qf], sorted order
-  o = align256(o + (shift ? (size_t)Qf * sizeof(float) : 0));
-  w.hrows = o;  // decoder input rows of the shifted encode, [Qf][K0] in the MLP's dtype
-  o = align256(o + (shift ? (size_t)Qf * M.K0 * (md == OO_F32 ? 4 : 2) : 0));
-  w.gdwp = o;
+  w.wdir = take(shift ? (size_t)Qb * sizeof(float4) : 0);
+  w.dd = take(shift ? (size_t)Qb * sizeof(float) : 0);
+  size_t P = 0;
   if (shift) {
     const oo_disparity* p = tree->disparity;
-    size_t P = (size_t)p->dims[1] * p->dims[0] + p->dims[1] + (size_t)p->dims[p->n_layers] * p->dims[p->n_layers - 1] +
-               p->dims[p->n_layers];
+    P = (size_t)p->dims[1] * p->dims[0] + p->dims[1] + (size_t)p->dims[p->n_layers] * p->dims[p->n_layers - 1] +
+        p->dims[p->n_layers];
     if (p->n_layers == 3) P += (size_t)p->dims[2] * p->dims[1] + p->dims[2];
-    o = align256(o + (size_t)w.ggrid * P * sizeof(float));
   }
+  w.gdwp = take((size_t)w.ggrid * P * sizeof(float));
   w.dcap = shift ? disparity_rows_cap(Qb) : 0;
-  w.drows = o;
-  o = align256(o + (size_t)disparity_rows_floats(w.dcap) * sizeof(float));
-  const size_t esz = md == OO_F32 ? 4 : 2;
-  for (int i = 0; i < M.n_layers; ++i) {
-    w.wt[i] = o;
-    o = align256(o + (size_t)w.PL.n_in[i] * ((w.PL.n_out[i] + 3) & ~3) * esz);
-  }
-  w.dwp = o;  // dW/db partials, [grid][P], accumulated over the backward's chunks
-  o = align256(o + (size_t)w.grid * w.PL.P * sizeof(float));
-  // spatially bucketed queries, written by the forward and read by both passes
-  const SortShape ss = sort_shape(Qf, L - 1, shift);
-  w.order = o;
-  o = align256(o + (size_t)Qf * sizeof(int32_t));
-  w.rank = o;
-  o = align256(o + (size_t)Qf * sizeof(int32_t));
-  w.scount = o;
-  o = align256(o + (size_t)ss.NB * ss.K * sizeof(int32_t));
-  w.stotal = o;
-  o = align256(o + (size_t)ss.K * sizeof(int32_t));
-  w.sstart = o;
-  o = align256(o + (size_t)ss.K * sizeof(int32_t));
+  w.drows = take((size_t)disparity_rows_floats(w.dcap) * sizeof(float));
+  for (int i = 0; i < M.n_layers; ++i)  // transposed weights of bwd_kernel
+    w.wt[i] = take(bwd16 ? 0 : (size_t)w.PL.n_in[i] * ((w.PL.n_out[i] + 3) & ~3) * esz);
+  w.dwp = take((size_t)w.grid * w.PL.P * sizeof(float));  // dW/db partials, [grid][P], accumulated over the chunks
   // coarse-level pair buffers of the feature-gradient scatter
-  w.gpad = o;
   w.pad_total = 0;
   bool open = tree->C == 8 && !paper;  // the paper's scheme scatters to vertices directly
   for (int l = 0; l < OO_MAX_LEVELS; ++l) {
@@ -435,8 +432,25 @@ Workspace workspace_layout(const MlpArgs& M, oo_dtype md, const oo_residual_batc
     w.pad_off[l] = w.pad_total;
     w.pad_total += f;
   }
-  o = align256(o + (size_t)w.pad_total * sizeof(float));
-  w.total = o;
+  w.gpad = take((size_t)w.pad_total * sizeof(float));
+  // spatially bucketed queries: the backward reads the order of its own
+  // queries, the first Qb; all that follows them is the forward's alone
+  const SortShape ss = sort_shape(Qf, L - 1, shift);
+  w.order = o;
+  w.dh = align256(o + (size_t)Qb * sizeof(int32_t));
+  take((size_t)Qf * sizeof(int32_t));
+  w.rank = take((size_t)Qf * sizeof(int32_t));
+  w.Lq = take((size_t)Qf * 3 * sizeof(float));
+  w.lossp = take((size_t)(combine_blocks(B, N) + 1) * sizeof(double));
+  w.scount = take((size_t)ss.NB * ss.K * sizeof(int32_t));
+  w.stotal = take((size_t)ss.K * sizeof(int32_t));
+  w.sstart = take((size_t)ss.K * sizeof(int32_t));
+  w.dsp = take(shift ? (size_t)Qf * sizeof(float) : 0);  // [Qf], sorted order
+  // decoder input rows of the shifted encode, [Qf][K0] in the MLP's dtype
+  w.hrows = take(shift ? (size_t)Qf * M.K0 * esz : 0);
+  // dLoss/dh of every backward query (staged: of one chunk's), [.][L C] FP32
+  w.chunks = bwd_chunks(Qb, bwd16, rows > o - std::min(o, w.dh));
+  w.total = std::max(o, align256(w.dh + (size_t)(w.chunks.staged ? w.chunks.size : Qb) * LC * sizeof(float)));
   return w;
 }
 
@@ -813,7 +827,8 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
     if (e == hipSuccess && G.n_levels) e = launch_fill_zero(reinterpret_cast<float*>(ws + w.dd), Qb, stream);
   }
   if (e != hipSuccess) return hip_status(e, "seed launch");
-  if (!runs_bwd16(M, mlp->dtype)) {
+  const bool bwd16 = runs_bwd16(M, mlp->dtype);
+  if (!bwd16) {
     ProfScope ps(OO_PROF_TRANSPOSE, stream);
     e = launch_transpose_weights(M, mlp->dtype, Wt, stream);
   }
@@ -822,20 +837,22 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
   const float4* pos = reinterpret_cast<const float4*>(ws + w.pos);
   float* dh = reinterpret_cast<float*>(ws + w.dh);
   GA.coarse = coarse_levels(T, GA, Qb);
-  // (the 16-bit backward fills a CU's registers and LDS: beside it the scatter
-  // gains nothing, and one launch of each takes 3458 us of a step of 2^20
-  // points x 9 where four of each on two streams took 3494)
-  const int nc = runs_bwd16(M, mlp->dtype) ? 1 : bwd_chunks(Qb);
-  const int64_t chunk = ((Qb + nc - 1) / nc + 63) / 64 * 64;  // whole 64-query tiles
+  const BwdChunks& ch = w.chunks;
+  const auto coarse = [&](int64_t q0, int64_t qn, const float* dhq) {
+    if (!GA.coarse) return hipSuccess;
+    ProfScope ps(OO_PROF_SCATTER, stream);
+    return launch_scatter_coarse(T, qn, nidx + q0, Qb, uv + q0, dhq, post_scale, GA, stream);
+  };
   {
     std::lock_guard<std::mutex> lk(g_side_m);
     SideStream* side = nullptr;
-    if (nc > 1 && (e = side_stream(side)) != hipSuccess) return hip_status(e, "side stream");
-    for (int c = 0; c < nc; ++c) {
-      const int64_t q0 = c * chunk, qn = std::min(Qb - q0, chunk);
+    if (!bwd16 && ch.n > 1 && (e = side_stream(side)) != hipSuccess) return hip_status(e, "side stream");
+    for (int c = 0; c < ch.n; ++c) {
+      const int64_t q0 = c * ch.size, qn = std::min(Qb - q0, ch.size);
       if (qn <= 0) break;
       const int64_t LC = (int64_t)tree->n_levels * tree->C;
-      BwdArgs B{qn, nidx + q0, Qb, uv + q0, pos + q0, seeds + 3 * q0, order + q0, partials, dh + q0 * LC, c > 0};
+      float* const dhq = ch.staged ? dh : dh + q0 * LC;
+      BwdArgs B{qn, nidx + q0, Qb, uv + q0, pos + q0, seeds + 3 * q0, order + q0, partials, dhq, c > 0};
       B.rows = ws + w.brows + (size_t)q0 * 4 * 2;
       B.gA = batch->attr;
       B.gB = A.N > 0 ? batch->attr2 : batch->attr;
@@ -861,16 +878,13 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
       }
       {
         ProfScope ps(OO_PROF_SCATTER, ss);
-        e = launch_scatter(T, tree->feat_dtype, qn, nidx + q0, Qb, uv + q0, pos + q0, dh + q0 * LC, post_scale, GA, SA,
-                           ss);
+        e = launch_scatter(T, tree->feat_dtype, qn, nidx + q0, Qb, uv + q0, pos + q0, dhq, post_scale, GA, SA, ss);
       }
       if (e != hipSuccess) return hip_status(e, "scatter launch");
+      if (ch.staged && (e = coarse(q0, qn, dhq)) != hipSuccess) return hip_status(e, "coarse scatter launch");
     }
-    if (GA.coarse) {  // beside the last chunk's scatter
-      ProfScope ps(OO_PROF_SCATTER, stream);
-      e = launch_scatter_coarse(T, Qb, nidx, uv, dh, post_scale, GA, stream);
-      if (e != hipSuccess) return hip_status(e, "coarse scatter launch");
-    }
+    // all of dh is there: one launch, beside the last chunk's scatter
+    if (!ch.staged && (e = coarse(0, Qb, dh)) != hipSuccess) return hip_status(e, "coarse scatter launch");
     if (side) {  // the caller's stream continues after the last scatter
       if ((e = hipEventRecord(side->ev[kMaxChunks], side->s)) != hipSuccess) return hip_status(e, "event record");
       if ((e = hipStreamWaitEvent(stream, side->ev[kMaxChunks], 0)) != hipSuccess) return hip_status(e, "stream wait");

@@ -887,7 +887,7 @@ struct CoarseArgs {
 };
 
 __global__ __launch_bounds__(kCoarseThreads) void scatter_coarse_kernel(const TreeArgs T, int64_t Q,
-                                                                        const int32_t* __restrict__ nidx,
+                                                                        const int32_t* __restrict__ nidx, int64_t ldn,
                                                                         const float2* __restrict__ uv,
                                                                         const float* __restrict__ dh, float post_scale,
                                                                         const GradArgs G, const CoarseArgs A) {
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(kCoarseThreads) void scatter_coarse_kernel(const Tr
   const int l = A.level[blockIdx.y], R = T.res[l], cells = (R + 1) * (R + 1);
   const int64_t q0 = (int64_t)blockIdx.x * A.run;
   const int n = (int)(Q - q0 < A.run ? Q - q0 : A.run);
-  const int32_t* const ids = nidx + (int64_t)l * Q + q0;
+  const int32_t* const ids = nidx + (int64_t)l * ldn + q0;
   if (tid == 0) {
     id_min = INT32_MAX;
     n_over = 0;
@@ -1031,16 +1031,21 @@ uint32_t coarse_levels(const TreeArgs& T, const GradArgs& G, int64_t Q) {
   return m;
 }
 
-hipError_t launch_scatter_coarse(const TreeArgs& T, int64_t Q, const int32_t* nidx, const float2* uv, const float* dh,
-                                 float post_scale, const GradArgs& G, hipStream_t st) {
+hipError_t launch_scatter_coarse(const TreeArgs& T, int64_t Q, const int32_t* nidx, int64_t ldn, const float2* uv,
+                                 const float* dh, float post_scale, const GradArgs& G, hipStream_t st) {
   CoarseArgs A;
   A.n = 0;
   A.run = coarse_run(T, G, Q);
   for (int l = 0; l < T.L; ++l)
-    if ((G.coarse >> l) & 1u) A.level[A.n++] = l;
+    if ((G.coarse >> l) & 1u) {
+      A.level[A.n++] = l;
+      // (a launch over part of the queries that coarse_levels looked at)
+      const int least = (2 * (T.res[l] + 1) * (T.res[l] + 1) + kCoarseThreads - 1) / kCoarseThreads * kCoarseThreads;
+      if (A.run < least) A.run = least;
+    }
   if (A.n == 0 || Q == 0) return hipSuccess;
   hipLaunchKernelGGL(scatter_coarse_kernel, dim3((unsigned)((Q + A.run - 1) / A.run), A.n), dim3(kCoarseThreads), 0, st,
-                     T, Q, nidx, uv, dh, post_scale, G, A);
+                     T, Q, nidx, ldn, uv, dh, post_scale, G, A);
   return hipGetLastError();
 }
 

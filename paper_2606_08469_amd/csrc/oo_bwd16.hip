@@ -2,8 +2,8 @@
 // weight gradients.
 //
 // Every wave carries 16 queries of its own through the whole chain in
-// registers, from the decoder inputs that the forward kept: the hidden
-// layers, then the gradient back through the transposed weights. Only the
+// registers, from the level features that the forward kept and the caller's
+// surface attributes: the hidden layers, then the gradient back through the transposed weights. Only the
 // weight gradients need the workgroup: dW of a layer is contracted over all
 // its queries, each wave owning a block of dW tiles in registers for the
 // whole kernel, so activations and deltas pass through LDS once per layer,
@@ -173,6 +173,7 @@ __global__ __launch_bounds__(64 * NW) void bwd16_kernel(const MlpArgs M, const i
   // ---- inputs: a lane's two runs of four inputs per chunk, and the seeds ----
   s16x4 raw[4][2];
   float sd[3];
+  int src_q = -1;  // source query, whose surface attributes the decoder reads
   const MT* const rows = reinterpret_cast<const MT*>(A.rows);
   auto load = [&](int64_t tile) {
     const int lane = threadIdx.x & 63;
@@ -181,12 +182,13 @@ __global__ __launch_bounds__(64 * NW) void bwd16_kernel(const MlpArgs M, const i
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {  // (columns past K0 read the first ones: masked below)
+      for (int hf = 0; hf < 2; ++hf) {  // (columns past L C read the first ones: masked below)
         const int col = 32 * kb + 16 * hf + 4 * (lane >> 4);
-        raw[kb][hf] = *reinterpret_cast<const s16x4*>(rows + ((col < K0 ? col >> 2 : 0) * A.ldn + qc) * 4);
+        raw[kb][hf] = *reinterpret_cast<const s16x4*>(rows + ((col < LC ? col >> 2 : 0) * A.ldn + qc) * 4);
       }
 #pragma unroll
     for (int i = 0; i < 3; ++i) sd[i] = A.seeds[3 * qc + i];
+    if (K0 > LC) src_q = A.order[qc];
   };
   const int64_t n_tiles = (A.Q + 16 * NW - 1) / (16 * NW);
   const TileRange rng = xcd_tiles(n_tiles, 1, 0);
@@ -204,9 +206,21 @@ __global__ __launch_bounds__(64 * NW) void bwd16_kernel(const MlpArgs M, const i
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
           const s16x4 zero = {0, 0, 0, 0};
-          const bool in = valid && 32 * kb + 16 * hf + 4 * g < K0;
+          const bool in = valid && 32 * kb + 16 * hf + 4 * g < LC;
           *reinterpret_cast<s16x4*>(A0w + (kb * 2 + hf) * kPlane + 4 * lane) = in ? raw[kb][hf] : zero;
         }
+    if (valid && src_q >= 0 && src_q < A.n_src) {  // surface attributes, in the caller's query order
+      const int E = K0 - LC;
+      const float* const gp = src_q < A.nA ? A.gA + (int64_t)E * src_q : A.gB + E * (src_q - A.nA);
+      for (int k = 4 * g; k < E; k += 16) {
+        typedef MT v4 __attribute__((ext_vector_type(4)));
+        const int col = LC + k;
+        v4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = from_f32<MT>(gp[k + j]);
+        *reinterpret_cast<s16x4*>(A0w + (col >> 4) * kPlane + 4 * ((col & 12) * 4 + r16)) = __builtin_bit_cast(s16x4, v);
+      }
+    }
     frag sf;  // seeds of the output layer, rows 0 .. 2
 #pragma unroll
     for (int i = 0; i < 8; ++i) sf[i] = from_f32<MT>(i < 3 && g == 0 && valid ? sd[i < 3 ? i : 0] : 0.0f);

@@ -137,7 +137,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C == 4 ? 4 
 #pragma unroll
     for (int c = 0; c < 4; ++c) v[c] = from_f32<MT>(g4[c]);
     *reinterpret_cast<v4*>(row + K0 - E + k) = v;
-    if (brow) *reinterpret_cast<v4*>(brow + (((K0 - E + k) >> 2) * O.n_idx + q) * 4) = v;
   }
 }
 

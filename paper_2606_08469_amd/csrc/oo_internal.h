@@ -69,7 +69,7 @@ struct QueryOut {
   float4* pos;
   float4* wdir;
   int64_t n_idx;
-  void* rows = nullptr;         // 16-bit operands: the decoder's inputs, [K0 / 4][n_idx][4], for the backward
+  void* rows = nullptr;         // 16-bit operands: the level features for the backward, [L C / 4][n_idx][4]
   const float* disp = nullptr;  // per-query disparity, read by the shifted encode into rows
 };
 // The predictor's d of Q queries into out[q * stride], in FP32 with every sum
@@ -142,7 +142,7 @@ struct BwdArgs {
   float* partials;
   float* dh;            // [Q][L C]: dLoss/dh of the level features
   int accumulate;
-  const void* rows = nullptr;  // 16-bit operands: the decoder's inputs that the forward kept, [K0 / 4][ldn][4]
+  const void* rows = nullptr;  // 16-bit operands: the level features that the forward kept, [L C / 4][ldn][4]
   // the decoder's surface attributes in the caller's query order: [nA][E]
   // for the first nA queries, [n_src - nA][E] for the rest
   const float* gA = nullptr;
@@ -174,10 +174,10 @@ hipError_t launch_scatter(const TreeArgs& T, oo_dtype td, int64_t Q, const int32
                           const float2* uv, const float4* pos, const float* dh, float post_scale, const GradArgs& G,
                           const ShiftArgs& S, hipStream_t st);
 // The levels with pair buffers on which many of the Q backward queries share
-// a footprint, and their scatter, over all queries in one launch.
+// a footprint, and their scatter over Q consecutive sorted positions.
 uint32_t coarse_levels(const TreeArgs& T, const GradArgs& G, int64_t Q);
-hipError_t launch_scatter_coarse(const TreeArgs& T, int64_t Q, const int32_t* nidx, const float2* uv, const float* dh,
-                                 float post_scale, const GradArgs& G, hipStream_t st);
+hipError_t launch_scatter_coarse(const TreeArgs& T, int64_t Q, const int32_t* nidx, int64_t ldn, const float2* uv,
+                                 const float* dh, float post_scale, const GradArgs& G, hipStream_t st);
 // Disparity predictor backward over the Q sorted backward queries (x, dir
 // from src; dd[q] = dLoss/d disparity), at most `cap` queries per pass
 // through the row buffer `rows` (disparity_rows_floats(cap) floats):

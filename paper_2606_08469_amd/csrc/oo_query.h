@@ -15,9 +15,9 @@ namespace oo {
 // In the paper's scheme the stored indices are the eight corner cells'
 // nodes per level ([L][8][n_idx]) and the query's position is kept too
 // (pos_out, [n_idx]); the scatter recomputes the trilinear weights from it.
-// With 16-bit operands the decoder's inputs are kept as well (O.rows,
-// [K0 / 4][n_idx][4]: a wave's stores are contiguous), so that the backward
-// gathers nothing.
+// With 16-bit operands the level features are kept as well (O.rows,
+// [L C / 4][n_idx][4]: a wave's stores are contiguous), so that the backward
+// gathers no texels.
 // MODE as for encode_kernel; with the shift rgb[3 q] holds query q's
 // disparity when the kernel starts (the wave that reads it writes the
 // radiance there).
@@ -162,12 +162,6 @@ __global__ __launch_bounds__(64 * query_waves<MT>(H, WLDS, MODE))
       float g4[4] = {0.f, 0.f, 0.f, 0.f};
       if (valid) load_attr4(src, q, k, g4);
       input4(M.K0 - M.E + k, g4);
-      if (sizeof(MT) == 2 && keep && brows) {
-        v4 v;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = from_f32<MT>(g4[c]);
-        *reinterpret_cast<v4*>(brows + (((M.K0 - M.E + k) >> 2) * n_idx + q) * 4) = v;
-      }
     }
     if constexpr (STREAM) {  // the rest of the last chunk
       const float z[4] = {0.f, 0.f, 0.f, 0.f};
