@@ -234,8 +234,11 @@ int oo_mlp_fwd(const oo_mlp* mlp, const void* h, oo_dtype h_dtype, int64_t B, fl
 /*
  * Fused query forward: encode + decode in one kernel. h stays on chip
  * (Sec. 3.6, rendering: one query and one decoder evaluation per visible
- * point).
- *  - x, dir: [B][3] FP32. rgb_out: [B][3] FP32.
+ * point). With a disparity predictor a kernel before it leaves each query's
+ * disparity in rgb_out (oo_query_fwd_ws is faster).
+ *  - x, dir: [B][3] FP32. rgb_out: [B][3] FP32; it may be the array x or
+ *    the array dir (with a predictor a slower kernel then runs alone), and
+ *    must not overlap the inputs otherwise.
  *  - attr: [B][E] FP32, the decoder's surface attributes g (E = dims[0] -
  *    n_levels * C); NULL when E = 0, required otherwise.
  *  - Supported type pairs (tree->feat_dtype, mlp->dtype): (F32, F32),

@@ -21,6 +21,8 @@ extern "C" {
  *  - oo_query_workspace_bytes: the size this needs for B queries (0 without
  *    a predictor; bounded, since large batches run in passes).
  *  - workspace_bytes smaller than that: OO_EINVAL, before any launch.
+ *  - rgb_out may be the array x or the array dir, as in oo_query_fwd; the
+ *    workspace overlaps none of the arrays.
  */
 int oo_query_workspace_bytes(const oo_tree* tree, const oo_mlp* mlp, int64_t B, size_t* bytes);
 int oo_query_fwd_ws(const oo_tree* tree, const oo_mlp* mlp, const float* x, const float* dir, const float* attr,

@@ -257,6 +257,33 @@ __device__ __forceinline__ void disp_hidden2(const DispArgs& G, const float* W0,
   }
 }
 
+// Predicted disparity d(x, w_r) of one lane's query (u = unit(w_r)), every
+// sum in the order of its inputs.
+__device__ __forceinline__ float predict_lane(const DispArgs& G, const float x[3], const float u[3]) {
+  float a[kDispK];
+  disparity_input(G, x, u, a);
+  // (selected, not indexed: a runtime index into the argument's arrays
+  // would copy them to scratch memory)
+  const bool two = G.n_layers == 3;
+  const float* Wo = two ? G.W[2] : G.W[1];
+  float d = (two ? G.b[2] : G.b[1])[0];
+  if (two) {
+    float z2[kDispH];
+    disp_hidden2(G, G.W[0], G.W[1], a, z2, [](int, const float (&)[kDispChunk]) {});
+#pragma unroll
+    for (int o = 0; o < kDispH; ++o) d += Wo[o] * fmaxf(z2[o], 0.0f);
+  } else {
+#pragma unroll 1
+    for (int c = 0; c < kDispH; c += kDispChunk) {
+      float h1[kDispChunk];
+      disp_chunk0(G, G.W[0], c, a, h1);
+#pragma unroll
+      for (int j = 0; j < kDispChunk; ++j) d += Wo[c + j] * h1[j];
+    }
+  }
+  return d;
+}
+
 // Unit vector of a direction (zero stays zero).
 __device__ __forceinline__ void unit_dir3(const float d[3], float u[3]) {
   const float n2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
