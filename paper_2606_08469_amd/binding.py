@@ -324,10 +324,14 @@ def query_fwd(tree: Tree, mlp: MLP, x, d, feat=None, W=None, out=None, attr=None
     if tree.disparity is not None:  # the split kernels, with a workspace from torch's allocator
         n = C.c_size_t(0)
         _check(lib().oo_query_workspace_bytes(C.byref(ts), C.byref(ms), B, C.byref(n)), "oo_query_workspace_bytes")
-        ws = torch.empty(max(n.value, 256), dtype=torch.uint8, device="cuda")
-        _check(lib().oo_query_fwd_ws(C.byref(ts), C.byref(ms), _ptr(x), _ptr(d), _ptr(attr), B, _ptr(rgb), _ptr(ws),
-                                     _nbytes(ws), _stream()), "oo_query_fwd_ws")
-        return rgb
+        try:
+            ws = torch.empty(max(n.value, 256), dtype=torch.uint8, device="cuda")
+        except torch.OutOfMemoryError:  # (up to 0.54 GB) the call without one gives the same, more slowly
+            ws = None
+        if ws is not None:
+            _check(lib().oo_query_fwd_ws(C.byref(ts), C.byref(ms), _ptr(x), _ptr(d), _ptr(attr), B, _ptr(rgb), _ptr(ws),
+                                         _nbytes(ws), _stream()), "oo_query_fwd_ws")
+            return rgb
     _check(lib().oo_query_fwd(C.byref(ts), C.byref(ms), _ptr(x), _ptr(d), _ptr(attr), B, _ptr(rgb), _stream()),
            "oo_query_fwd")
     return rgb

@@ -1,4 +1,5 @@
-"""Queries whose radiance goes where their positions or directions were."""
+"""Queries whose radiance goes where their positions or directions were, and
+queries without memory for a workspace."""
 import ctypes
 
 import pytest
@@ -46,3 +47,23 @@ def test_radiance_over_an_input(predictor, dtype, B):
         ins = [over if at == i else t for i, t in enumerate((x, d))]
         assert torch.equal(binding.query_fwd(model.tree, model.mlp, *ins, feat=model.work_feat, W=model.work_W,
                                              out=over, attr=attr), want)
+
+
+def test_query_without_room_for_a_workspace(monkeypatch):
+    """binding.query_fwd where the device has no memory left for the workspace
+    of a model with a predictor: the call that needs none, same bits."""
+    model, _, _ = small_paper_model(torch.float16, (64, 64))
+    x, d, attr = torch.rand(999, 3).cuda(), torch.randn(999, 3).cuda(), torch.randn(999, 4).cuda()
+    out = torch.empty(999, 3, device="cuda")
+    want = model(x, d, attr).clone()
+    empty = torch.empty
+
+    def no_room(*size, **kw):
+        if kw.get("dtype") == torch.uint8:
+            raise torch.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", no_room)
+    print("[case] query without room for a workspace", flush=True)
+    got = binding.query_fwd(model.tree, model.mlp, x, d, feat=model.work_feat, W=model.work_W, out=out, attr=attr)
+    assert got is out and torch.equal(got, want)
