@@ -15,12 +15,13 @@ extern "C" {
  * oo_query_fwd with a workspace (device memory of the caller, free again
  * when the work on `stream` has passed the call). With a disparity predictor
  * the queries then run as three kernels (predictor, shifted encode into
- * decoder input rows, decoder), several times faster than the fused one;
- * trees without a predictor run the fused kernel and need no workspace. The
- * results are those of oo_query_fwd.
+ * decoder input rows, decoder), in half the time (1280x720 in FP16: 0.59 ms,
+ * 1.22 without a workspace); trees without a predictor run the fused kernel
+ * and need no workspace. The results are those of oo_query_fwd.
  *  - oo_query_workspace_bytes: the size this needs for B queries (0 without
  *    a predictor; bounded, since large batches run in passes).
- *  - workspace_bytes smaller than that: OO_EINVAL, before any launch.
+ *  - workspace: 16-byte aligned. One that is not, or workspace_bytes smaller
+ *    than that: OO_EINVAL, before any launch.
  *  - rgb_out may be the array x or the array dir, as in oo_query_fwd; the
  *    workspace overlaps none of the arrays.
  */

@@ -667,6 +667,7 @@ int oo_query_fwd_ws(const oo_tree* tree, const oo_mlp* mlp, const float* x, cons
   if (!workspace || workspace_bytes < need)
     return fail(OO_EINVAL, "workspace of %zu bytes is smaller than the %zu this problem needs",
                 workspace ? workspace_bytes : 0, need);
+  if (reinterpret_cast<uintptr_t>(workspace) % 16) return fail(OO_EINVAL, "workspace is not 16-byte aligned");
   float* const disp = static_cast<float*>(workspace);
   void* const rows = static_cast<char*>(workspace) + rows_at;
   ProfScope ps(OO_PROF_QUERY, stream);
