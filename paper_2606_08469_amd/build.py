@@ -20,7 +20,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-result", "-Wno-unused-value",
+    "-Wall", "-Wno-unused-result", "-Werror=unused-value",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 

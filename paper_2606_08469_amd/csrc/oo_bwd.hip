@@ -687,17 +687,6 @@ __device__ inline void bsdf_weight_b(const ResidualArgs& A, int64_t b, int k, fl
 // Launchers
 // ---------------------------------------------------------------------------
 
-static int cu_count() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    hipGetDevice(&dev);
-    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (cus <= 0) cus = 256;
-  }
-  return cus;
-}
-
 constexpr size_t kLdsBytes = 160 * 1024;
 
 // LDS of the backward workgroup: the buffers, plus the packed hidden weights
@@ -717,7 +706,7 @@ bool runs_bwd16(const MlpArgs& M, oo_dtype md) { return md != OO_F32 && bwd16_sh
 // there is one dW partial per resident workgroup (LDS bound, 160 KiB per CU
 // on gfx950; the 16-bit kernels run one workgroup per CU).
 int bwd_grid(const MlpArgs& M, oo_dtype md, int L, int64_t Q) {
-  int64_t n_tiles, g = cu_count();
+  int64_t n_tiles, g = device_cus();
   if (runs_bwd16(M, md)) {
     const int rows = 16 * bwd16_shape(M).waves;
     n_tiles = (Q + rows - 1) / rows;
@@ -756,7 +745,7 @@ template <class MT, int C, int H, bool WL, int NHH>
 static hipError_t launch_bwd_k(const TreeArgs& T, const MlpArgs& M, const MlpArgs& Mt, const BwdArgs& A,
                                const ParamLayout& PL, int grid, size_t lds, hipStream_t st) {
   auto k = T.interp == OO_INTERP_PAPER ? bwd_kernel<MT, MT, C, H, WL, true, NHH> : bwd_kernel<MT, MT, C, H, WL, false, NHH>;
-  hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  allow_lds((const void*)k, lds);
   hipLaunchKernelGGL(k, dim3(grid), dim3(64 * bwd_waves<MT>()), lds, st, T, M, Mt, A, PL);
   return hipGetLastError();
 }
@@ -1016,7 +1005,7 @@ __global__ __launch_bounds__(kCoarseThreads) void scatter_coarse_kernel(const Tr
 static int coarse_run(const TreeArgs& T, const GradArgs& G, int64_t Q) {
   int padded = 0;
   for (int l = 0; l < T.L; ++l) padded += G.pad[l] != nullptr;
-  const int64_t run = (Q * padded / cu_count() + kCoarseThreads - 1) / kCoarseThreads * kCoarseThreads;
+  const int64_t run = (Q * padded / device_cus() + kCoarseThreads - 1) / kCoarseThreads * kCoarseThreads;
   return (int)(run < kCoarseRunMin ? kCoarseRunMin : (run > kCoarseRun ? kCoarseRun : run));
 }
 

@@ -398,7 +398,7 @@ static hipError_t launch_bwd16_t(const MlpArgs& M, int LC, const BwdArgs& A, con
            : M.n_layers == 3 ? bwd16_kernel<MT, H, 8, 1>
            : M.n_layers == 4 ? bwd16_kernel<MT, H, NWD, 2>
                              : bwd16_kernel<MT, H, NWD, 3>;
-  hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
+  allow_lds((const void*)k, s.lds);
   hipLaunchKernelGGL(k, dim3(grid), dim3(64 * s.waves), s.lds, st, M, LC, A, PL, s.nput);
   return hipGetLastError();
 }

@@ -52,6 +52,11 @@ struct ReduceDst {
 // Compute units of the device, and the LDS a workgroup may use.
 int device_cus();
 int max_lds();
+// Lets a kernel be launched with `lds` bytes of dynamic LDS (a refusal shows
+// as the launch's own error).
+inline void allow_lds(const void* kernel, size_t lds) {
+  (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
 
 hipError_t launch_encode(const TreeArgs& T, oo_dtype td, const float* x, const float* d, int64_t B, void* h,
                          oo_dtype hd, int32_t* idx, const DispArgs& G, hipStream_t st);

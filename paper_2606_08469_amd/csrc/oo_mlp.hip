@@ -80,25 +80,19 @@ __global__ __launch_bounds__(512) void mlp_kernel(const MlpArgs M, const MT* __r
   }
 }
 
+// An attribute of the current device, or `otherwise` where it cannot be read.
+static int device_attribute(hipDeviceAttribute_t a, int otherwise) {
+  int dev = 0, v = 0;
+  return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, a, dev) == hipSuccess && v > 0 ? v : otherwise;
+}
+
 int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    hipGetDevice(&dev);
-    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (cus <= 0) cus = 256;
-  }
+  static const int cus = device_attribute(hipDeviceAttributeMultiprocessorCount, 256);
   return cus;
 }
 
 int max_lds() {
-  static int lds = 0;
-  if (!lds) {
-    int dev = 0;
-    hipGetDevice(&dev);
-    hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    if (lds <= 0) lds = 65536;
-  }
+  static const int lds = device_attribute(hipDeviceAttributeMaxSharedMemoryPerBlock, 65536);
   return lds;
 }
 
@@ -117,7 +111,7 @@ static hipError_t launch_mlp_k(const MlpArgs& M, const void* h, int64_t Q, float
   auto k = mlp_kernel<MT, H, KB0, true>;
   if constexpr (may_not_fit)
     if (!wlds) k = mlp_kernel<MT, H, KB0, false>;
-  hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  allow_lds((const void*)k, lds);
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(512), lds, st, M, reinterpret_cast<const MT*>(h), Q, rgb);
   return hipGetLastError();
 }

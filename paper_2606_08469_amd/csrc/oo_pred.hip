@@ -238,10 +238,10 @@ hipError_t launch_disparity_fwd(const DispArgs& G, oo_dtype md, const QuerySrc& 
   const size_t lds = bias_bytes(P) + wbytes + (size_t)waves * 4 * kbt * kWave * 8 * sizeof(float);
   const int grid = tile_grid((Q + 63) / 64, lds);
   if (split) {
-    hipFuncSetAttribute((const void*)disparity_fwd_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    allow_lds((const void*)disparity_fwd_kernel<true>, lds);
     hipLaunchKernelGGL(disparity_fwd_kernel<true>, dim3(grid), dim3(64 * waves), lds, st, G, P, src, Q, d_out);
   } else {
-    hipFuncSetAttribute((const void*)disparity_fwd_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    allow_lds((const void*)disparity_fwd_kernel<false>, lds);
     hipLaunchKernelGGL(disparity_fwd_kernel<false>, dim3(grid), dim3(64 * waves), lds, st, G, P, src, Q, d_out);
   }
   return hipGetLastError();
@@ -404,7 +404,7 @@ hipError_t launch_predict(const DispArgs& G, const QuerySrc& src, int64_t Q, flo
   if (Q == 0) return hipSuccess;
   const size_t lds = (size_t)predict_frags(G.n_layers) * kWave * sizeof(f32x4) +
                      (3 * kDispH + kPredWaves * kDispK * kPredStride) * sizeof(float);
-  hipFuncSetAttribute((const void*)predict_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  allow_lds((const void*)predict_kernel, lds);
   hipLaunchKernelGGL(predict_kernel, dim3(tile_grid((Q + 63) / 64, lds)), dim3(64 * kPredWaves), lds, st, G, src, Q,
                      out, stride);
   return hipGetLastError();

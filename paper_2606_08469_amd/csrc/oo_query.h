@@ -252,11 +252,11 @@ static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const Quer
   }
   if (wlds) {
     auto k = query_kernel<MT, C, H, true, MODE >= 2 ? 1 : MODE, KEEP>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    allow_lds((const void*)k, lds);
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O, G);
   } else {
     auto k = query_kernel<MT, C, H, false, MODE, KEEP>;
-    hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    allow_lds((const void*)k, lds);
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), lds, st, T, M, src, Q, rgb, O, G);
   }
   return hipGetLastError();
