@@ -48,9 +48,8 @@ constexpr int query_waves_per_simd(int H, bool wlds, int mode) {
 }
 
 // KEEP: queries q < n_idx of this launch are the backward's. The residual
-// forward runs the others in a launch of their own, without the stores, from
-// kSplitMin queries on.
-constexpr int64_t kSplitMin = 1 << 15;
+// forward runs the others in a launch of their own, without the stores, where
+// that pays (split_queries).
 template <class MT, int C, int H, bool WLDS, int MODE, bool KEEP>
 __global__ __launch_bounds__(64 * query_waves<MT>(H, WLDS, MODE))
     __attribute__((amdgpu_waves_per_eu(query_waves_per_simd<MT>(H, WLDS, MODE)))) void query_kernel(
@@ -238,6 +237,30 @@ static void tile_launch_shape(const MlpArgs& M, int mode, int64_t Q, bool& wlds,
   grid = tile_grid((Q + 63) / 64, lds);
 }
 
+// Whether the Q - n queries after the first n run in a launch of their own,
+// whose kernel stores nothing for the backward. It pays where it costs no
+// more rounds of the chip (tiles that a workgroup has time for, idle ones
+// among them), or where the second launch is long enough to make up for one
+// that is mostly idle: eight rounds, or three with streamed 16-bit layers,
+// whose rounds the stores slow down by a fifth. Training steps without the
+// split and with it: FP32, 128-wide, 4,000 points x 8 354 and 455 us, 100,000
+// x 4 1414 and 1488; FP16, 64-wide, 60,000 x 3 257 and 264, 200,000 x 4 619 and
+// 588, 262,144 x 4 694 and 652.
+template <class MT>
+static bool split_queries(const MlpArgs& M, int mode, int64_t n, int64_t Q) {
+  int64_t rounds = 0;
+  auto slots = [&](int64_t q) {
+    bool wlds;
+    int waves, grid;
+    size_t lds;
+    tile_launch_shape<MT>(M, mode, q, wlds, waves, lds, grid);
+    const int64_t tiles = (q + 63) / 64, round = (int64_t)grid * waves;
+    rounds = tiles / round;
+    return (tiles + round - 1) / round * waves;
+  };
+  const int64_t all = slots(Q), kept = slots(n), rest = slots(Q - n);
+  return kept + rest <= all || rounds >= (query_streams(M.H, true, mode) && sizeof(MT) == 2 ? 3 : 8);
+}
 
 template <class MT, int C, int H, int MODE, bool KEEP>
 static hipError_t launch_query_p(const TreeArgs& T, const MlpArgs& M, const QuerySrc& src, int64_t Q, float* rgb,
@@ -283,9 +306,8 @@ static hipError_t launch_query_t(const TreeArgs& T, const MlpArgs& M, const Quer
   }
   const bool paper = T.interp == OO_INTERP_PAPER;
   if (O.n_idx > 0) {
-    // (few queries: all in one launch; steps of 2,000 queries take 185 us in
-    // FP32 and 163 in FP16 with a second one, 157 and 146 without)
-    const int64_t n = O.n_idx < Q && Q > kSplitMin ? O.n_idx : Q;
+    int64_t n = O.n_idx < Q ? O.n_idx : Q;
+    if (n < Q && !split_queries<MT>(M, paper, n, Q)) n = Q;
     const hipError_t e = paper ? launch_query_p<MT, C, H, 1, true>(T, M, src, n, rgb, O, G, st)
                                : launch_query_p<MT, C, H, 0, true>(T, M, src, n, rgb, O, G, st);
     if (e != hipSuccess || n == Q) return e;

@@ -13,10 +13,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("interp", [binding.INTERP_NODE_BILINEAR, binding.INTERP_PAPER])
-@pytest.mark.parametrize("B,N", [(16384, 1), (16385, 1), (8193, 3)])
+@pytest.mark.parametrize("B,N", [(16384, 1), (16385, 1), (8193, 3), (100003, 4), (262081, 3), (262144, 1), (200001, 5)])
 def test_two_query_launches(dtype, interp, B, N):
-    """The backward's and the secondary queries in one launch (2^15 queries)
-    and in two (more): what a query gives does not depend on it. LHS radiance
+    """The backward's and the secondary queries in one launch (up to 100,003
+    points here) and in two (the others: equally many rounds, or enough of
+    them): what a query gives does not depend on it. LHS radiance
     equal to the plain query's to the bit, the targets to those of the first
     points in a batch of their own (one launch), node indices to the
     oracle's."""
