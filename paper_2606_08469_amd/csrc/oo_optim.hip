@@ -48,47 +48,64 @@ __device__ inline void adam_quad(const AdamArgs& A, int64_t tq) {
 // elements (8.9 GB): 1571 us, 5.7 TB/s (1679 if the working copy is stored
 // through the caches); without the cache bypass 1761, looping
 // over 16,384 workgroups 1868, neither (and a search of the segments and a
-// 64-bit division per thread) 2112. Two or four quads per thread: 1577, 1615.
+// 64-bit division per thread) 2112.
+// A workgroup has two waves, each thread two quads one after the other: where
+// few maps were read, the time goes to starting waves that find nothing to do
+// (the same elements, a thousandth of them read: 156 us; with four waves of
+// one quad per thread 271, a tenth read 225 and 305, all of them 1709 and
+// 1703; with four quads per thread 97, 213 and 1739 to 1826).
+constexpr int kAdamThreads = 128, kAdamQuads = 2;
 template <class WT>
-__global__ __launch_bounds__(256) void adam_kernel(const AdamArgs A) {
+__global__ __launch_bounds__(kAdamThreads) void adam_kernel(const AdamArgs A) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   typedef WT w4 __attribute__((ext_vector_type(4)));
   const int64_t total = A.first[A.n_segs];
-  for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
+  constexpr int per = kAdamThreads * kAdamQuads;
+  for (int64_t base = (int64_t)blockIdx.x * per; base < total; base += (int64_t)gridDim.x * per) {
     int s = 0;
     while (s + 1 < A.n_segs && base >= A.first[s + 1]) ++s;
     const AdamSeg& S = A.seg[s];
     const int64_t q0 = base - A.first[s];
-    if (!S.vec || (q0 + 256) * 4 > S.n) {  // several segments, a short quad or unaligned arrays
-      if (base + threadIdx.x < total) adam_quad<WT>(A, base + threadIdx.x);
+    if (!S.vec || (q0 + per) * 4 > S.n) {  // several segments, a short quad or unaligned arrays
+      for (int64_t q = base + threadIdx.x; q < base + per && q < total; q += kAdamThreads) adam_quad<WT>(A, q);
       continue;
     }
-    const int64_t i0 = (q0 + threadIdx.x) * 4;
-    if (S.touched && !S.touched[S.shift >= 0 ? i0 >> S.shift : i0 / S.block]) continue;
-    f4* const pp = reinterpret_cast<f4*>(S.param + i0);
-    f4* const mp = reinterpret_cast<f4*>(S.m + i0);
-    f4* const vp = reinterpret_cast<f4*>(S.v + i0);
-    f4* const gp = reinterpret_cast<f4*>(S.grad + i0);
-    const f4 p0 = __builtin_nontemporal_load(pp), m0 = __builtin_nontemporal_load(mp);
-    const f4 v0 = __builtin_nontemporal_load(vp), g = __builtin_nontemporal_load(gp);
-    f4 p, m, v;
+    uint32_t go[kAdamQuads];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float pj = p0[j], mj = m0[j], vj = v0[j];
-      adam_update(A, pj, mj, vj, g[j]);
-      p[j] = pj;
-      m[j] = mj;
-      v[j] = vj;
+    for (int u = 0; u < kAdamQuads; ++u) {
+      const int64_t i0 = (q0 + kAdamThreads * u + threadIdx.x) * 4;
+      go[u] = S.touched ? S.touched[S.shift >= 0 ? i0 >> S.shift : i0 / S.block] : 1u;
     }
-    __builtin_nontemporal_store(p, pp);
-    __builtin_nontemporal_store(m, mp);
-    __builtin_nontemporal_store(v, vp);
-    __builtin_nontemporal_store(f4{0.f, 0.f, 0.f, 0.f}, gp);
-    if (S.work) {
-      w4 w;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = from_f32<WT>(p[j]);
-      __builtin_nontemporal_store(w, reinterpret_cast<w4*>(reinterpret_cast<WT*>(S.work) + i0));
+    for (int u = 0; u < kAdamQuads; ++u) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (!go[u]) continue;
+      const int64_t i0 = (q0 + kAdamThreads * u + threadIdx.x) * 4;
+      f4* const pp = reinterpret_cast<f4*>(S.param + i0);
+      f4* const mp = reinterpret_cast<f4*>(S.m + i0);
+      f4* const vp = reinterpret_cast<f4*>(S.v + i0);
+      f4* const gp = reinterpret_cast<f4*>(S.grad + i0);
+      const f4 p0 = __builtin_nontemporal_load(pp), m0 = __builtin_nontemporal_load(mp);
+      const f4 v0 = __builtin_nontemporal_load(vp), g = __builtin_nontemporal_load(gp);
+      f4 p, m, v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float pj = p0[j], mj = m0[j], vj = v0[j];
+        adam_update(A, pj, mj, vj, g[j]);
+        p[j] = pj;
+        m[j] = mj;
+        v[j] = vj;
+      }
+      __builtin_nontemporal_store(p, pp);
+      __builtin_nontemporal_store(m, mp);
+      __builtin_nontemporal_store(v, vp);
+      __builtin_nontemporal_store(f4{0.f, 0.f, 0.f, 0.f}, gp);
+      if (S.work) {
+        w4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = from_f32<WT>(p[j]);
+        __builtin_nontemporal_store(w, reinterpret_cast<w4*>(reinterpret_cast<WT*>(S.work) + i0));
+      }
     }
   }
 }
@@ -96,14 +113,15 @@ __global__ __launch_bounds__(256) void adam_kernel(const AdamArgs A) {
 hipError_t launch_adam(const AdamArgs& A, oo_dtype wd, hipStream_t st) {
   const int64_t total = A.first[A.n_segs];
   if (total == 0) return hipSuccess;
-  int64_t blocks = (total + 255) / 256;
+  constexpr int per = kAdamThreads * kAdamQuads;
+  int64_t blocks = (total + per - 1) / per;
   if (blocks > 1 << 22) blocks = 1 << 22;  // (2^32 elements; more loop)
   if (wd == OO_F16)
-    hipLaunchKernelGGL(adam_kernel<f16>, dim3((unsigned)blocks), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(adam_kernel<f16>, dim3((unsigned)blocks), dim3(kAdamThreads), 0, st, A);
   else if (wd == OO_BF16)
-    hipLaunchKernelGGL(adam_kernel<bf16>, dim3((unsigned)blocks), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(adam_kernel<bf16>, dim3((unsigned)blocks), dim3(kAdamThreads), 0, st, A);
   else
-    hipLaunchKernelGGL(adam_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(adam_kernel<float>, dim3((unsigned)blocks), dim3(kAdamThreads), 0, st, A);
   return hipGetLastError();
 }
 
