@@ -182,21 +182,17 @@ def main():
     # two footprint rows of 2 texels, each one 64-byte chunk when it starts on
     # an even texel and two otherwise (1.5 on average); a 2x2 map is 2 chunks,
     # and so is a level whose gradients go through the library's pair buffers;
-    # levels whose shared footprints are summed before they go out send fewer
-    # and are left out (their launch counts in the time)
+    # levels whose shared footprints are summed before they go out send fewer,
+    # from a launch of their own, and are left out
     per_level = (idx[:B] >= 0).sum(0).to(torch.float64).cpu().numpy()
     paired = pair_buffered_levels(cfg, np.diff(lo))
-    merged = merged_levels(cfg, np.diff(lo), paired, B)
+    merged = merged_levels(cfg, np.diff(lo), paired, B, torch.cuda.get_device_properties(dev).multi_processor_count)
     atomic_req = float(sum(n * (2.0 if (r == 2 or l in paired) else 3.0)
                            for l, (n, r) in enumerate(zip(per_level, cfg.res)) if l not in merged))
     del xq, dq, idx, present
     kern = kernel_rooflines(cfg, B, Q, lv_all, lv_lhs, per_kernel)
     if "scatter" in kern:
-        k = kern["scatter"]
-        req = atomic_req / k["launches_per_step"]
-        rate = req / (k["ms_per_launch"] * 1e-3) / 1e9
-        k.update(atomic_requests=int(req), atomic_Greq_s=round(rate, 2), atomic_ceiling_Greq_s=ATOMIC_GREQ_S,
-                 frac_of_atomic_ceiling=round(rate / ATOMIC_GREQ_S, 4))
+        kern["scatter"].update(atomic_rate(kern["scatter"], atomic_req, merged))
     # the dominant kernel: most launch time per step
     dom = max(kern, key=lambda k: kern[k]["ms_per_step"])
     roof = {"kernel": dom, **kern[dom], "kernels": kern,
@@ -567,14 +563,26 @@ def pair_buffered_levels(cfg, nodes_per_level):
     return out
 
 
-def merged_levels(cfg, nodes_per_level, paired, B):
+def atomic_rate(scatter, requests, merged):
+    """The atomic requests a step's scatter sends, and their rate against the
+    ceiling. Where the merged levels have a launch of their own, the scatter's
+    time covers both kernels and the requests of one are not counted: a rate
+    would describe neither, so there is none (kernel traces tell them apart)."""
+    if merged:
+        return {"atomic_requests": int(requests), "merged_levels": sorted(merged)}
+    rate = requests / (scatter["ms_per_step"] * 1e-3) / 1e9
+    return {"atomic_requests": int(requests), "atomic_Greq_s": round(rate, 2), "atomic_ceiling_Greq_s": ATOMIC_GREQ_S,
+            "frac_of_atomic_ceiling": round(rate / ATOMIC_GREQ_S, 4)}
+
+
+def merged_levels(cfg, nodes_per_level, paired, B, compute_units):
     """Pair-buffered levels on which the library sums the footprints that
     several of the B points share before the atomic adds: from 2^17 points
     on, where a level has at least two points per footprint, over all its
     nodes and within the run of points a workgroup takes over one."""
     if B < 1 << 17:
         return set()
-    run = min(max(-(-B * len(paired) // (256 * 1024)) * 1024, 4096), 16384)
+    run = min(max(-(-(B * len(paired) // compute_units) // 1024) * 1024, 4096), 16384)
     cells = [(r + 1) ** 2 for r in cfg.res]
     return {l for l in paired if run >= 2 * cells[l] and B >= 2 * int(nodes_per_level[l]) * cells[l]}
 
