@@ -349,7 +349,11 @@ int oo_radiosity_residual_fwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
  *    ordered by events: it starts after that chunk's decoder backward on
  *    `stream`, and `stream` waits for the last scatter before the dW/db
  *    reduction. The other 16-bit decoders run on `stream` alone, in one
- *    chunk, or in two where the workspace holds dLoss/dh of one at a time.
+ *    chunk. With few secondary queries per backward query (2 bytes per level
+ *    feature of the backward queries are more than 20 per query of the batch
+ *    less 4 per backward query) it takes a workspace larger than
+ *    oo_residual_workspace_bytes says, by at most those 2 bytes per level
+ *    feature; with less, dLoss/dh is there for one of two chunks at a time.
  *    To the caller the call behaves as work enqueued on `stream`.
  */
 int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_residual_batch* batch,

@@ -345,6 +345,24 @@ def residual_workspace_bytes(tree: Tree, mlp: MLP, batch: dict, feat=None, W=Non
     return int(n.value)
 
 
+def _workspace(tree: Tree, mlp: MLP, batch: dict, feat=None, W=None):
+    """A workspace of the size the library asks for or, where it makes the
+    backward faster and there is memory for it, large enough for one chunk."""
+    n = residual_workspace_bytes(tree, mlp, batch, feat=feat, W=W)
+    W = mlp.W if W is None else W
+    B, N = batch["x"].shape[0], 0 if batch.get("target_override") is not None else int(batch.get("N", 0))
+    Qf = B * (1 + N)
+    Qb = Qf if batch.get("grad_through_rhs") else B
+    kept = 2 * tree.n_levels * tree.C * Qb
+    kept_by_forward = W[0].element_size() == 2 and not (len(W) == 5 and W[0].shape[0] == 128 and W[0].shape[1] > 96)
+    if kept_by_forward and tree.disparity is None and Qb >= 1 << 16 and kept > 20 * Qf - 4 * Qb:
+        try:
+            return torch.empty(n + kept, dtype=torch.uint8, device="cuda")
+        except torch.OutOfMemoryError:
+            pass
+    return torch.empty(max(n, 256), dtype=torch.uint8, device="cuda")
+
+
 def residual_fwd(tree: Tree, mlp: MLP, batch: dict, workspace, feat=None, W=None, outs=None):
     """Returns (lhs, rhs, resid) [B][3] FP32 and the loss (0-dim FP64 device tensor)."""
     B = batch["x"].shape[0]
@@ -579,13 +597,12 @@ class OctaOctree(torch.nn.Module):
         call may overwrite what an earlier one left there."""
         n = residual_workspace_bytes(self.tree, self.mlp, batch, feat=self.work_feat, W=self.work_W)
         if self._ws is None or self._ws.numel() < n:
-            self._ws = torch.empty(max(n, 256), dtype=torch.uint8, device="cuda")
+            self._ws = _workspace(self.tree, self.mlp, batch, feat=self.work_feat, W=self.work_W)
         return self._ws
 
     def new_workspace(self, batch):
         """A workspace of its own for one forward/backward pair."""
-        n = residual_workspace_bytes(self.tree, self.mlp, batch, feat=self.work_feat, W=self.work_W)
-        return torch.empty(max(n, 256), dtype=torch.uint8, device="cuda")
+        return _workspace(self.tree, self.mlp, batch, feat=self.work_feat, W=self.work_W)
 
     def residual(self, batch):
         """Loss of the residual step (0-dim FP64) with autograd to the masters."""

@@ -32,9 +32,11 @@ thread_local char g_err[512] = "";
 //    gains nothing: one chunk (a step of 2^20 points x 9 takes 3420 us; in
 //    four chunks on two streams 3494). Where the kept level features take
 //    more than the forward's scratch gives back (few secondary queries per
-//    backward query), two chunks one after the other, with dh for one of
-//    them: so no batch needs more than features, scratch and dh side by side
-//    less the features. The same step in two such chunks takes 3507 us.
+//    backward query), a caller with no more room than oo_residual_workspace_bytes
+//    asks for gets two chunks one after the other, with dh for one of them: so
+//    no batch needs more than features, scratch and dh side by side less the
+//    features. Steps in one chunk and in two: 140,000 points x 2 375 and 418 us,
+//    262,144 x 5 608 and 667, 2^20 x 3 2550 and 2620.
 constexpr int kMaxChunks = 4;
 constexpr int64_t kChunkQueries = 32768;
 
@@ -326,6 +328,7 @@ size_t query_workspace(int64_t pass, const MlpArgs& M, oo_dtype md, size_t& rows
 
 struct Workspace {
   size_t Lq, lossp, seeds, nidx, uv, pos, dh, wt[OO_MAX_LAYERS], dwp, order, rank, scount, stotal, sstart, gpad, total;
+  size_t unstaged;  // bytes that hold dh of every backward query
   size_t brows;  // bwd16_kernel: the level features of every backward query, [L C / 4][Qb][4] in 16 bits
   size_t wdir, dd, gdwp, dsp, drows, hrows;  // the disparity predictor's: lookup directions, dLoss/d
                                              // disparity, parameter partials, disparity of every query,
@@ -449,8 +452,10 @@ Workspace workspace_layout(const MlpArgs& M, oo_dtype md, const oo_residual_batc
   // decoder input rows of the shifted encode, [Qf][K0] in the MLP's dtype
   w.hrows = take(shift ? (size_t)Qf * M.K0 * esz : 0);
   // dLoss/dh of every backward query (staged: of one chunk's), [.][L C] FP32
+  w.unstaged = std::max(o, w.dh + (size_t)Qb * LC * sizeof(float));
   w.chunks = bwd_chunks(Qb, bwd16, rows > o - std::min(o, w.dh));
-  w.total = std::max(o, align256(w.dh + (size_t)(w.chunks.staged ? w.chunks.size : Qb) * LC * sizeof(float)));
+  w.total = w.chunks.staged ? std::max(o, align256(w.dh + (size_t)w.chunks.size * LC * sizeof(float)))
+                            : align256(w.unstaged);
   return w;
 }
 
@@ -838,7 +843,7 @@ int oo_radiosity_residual_bwd(const oo_tree* tree, const oo_mlp* mlp, const oo_r
   const float4* pos = reinterpret_cast<const float4*>(ws + w.pos);
   float* dh = reinterpret_cast<float*>(ws + w.dh);
   GA.coarse = coarse_levels(T, GA, Qb);
-  const BwdChunks& ch = w.chunks;
+  const BwdChunks ch = w.chunks.staged && workspace_bytes >= w.unstaged ? bwd_chunks(Qb, bwd16, false) : w.chunks;
   const auto coarse = [&](int64_t q0, int64_t qn, const float* dhq) {
     if (!GA.coarse) return hipSuccess;
     ProfScope ps(OO_PROF_SCATTER, stream);

@@ -132,3 +132,83 @@ def test_chunks_add_up(scheme, dtype, widths, n_attr, N, full):
     report(f"chunks {scheme} {dtype} {widths} N={N}", worst=worst)
     assert all(b.norm() > 0 for b in want[:4])
     assert worst <= bar
+
+
+@pytest.mark.parametrize("scheme", ["texels", "vertices"])
+@pytest.mark.parametrize("dtype,widths,n_attr,C", [(torch.float16, (64, 64), 4, 8), (torch.bfloat16, (128, 128, 128), 16, 4),
+                                                   (torch.float16, (128,) * 4, 72, 4)])
+@pytest.mark.parametrize("N,full", [(0, 0), (1, 0), (1, 1)])
+def test_smallest_workspace(scheme, dtype, widths, n_attr, C, N, full):
+    """140,002 backward queries in a workspace of the size the library asks
+    for (two chunks one after the other, dLoss/dh of one at a time) and in one
+    with room for a single chunk: the same forward, and gradients whose sums
+    differ in order alone (the bar of test_chunks_add_up). Nothing is written
+    past the workspace, and a second backward gives what the first did."""
+    if C == 4 and N == 1 and not full:
+        pytest.skip("the forward's scratch holds dLoss/dh of all queries")
+    B = 140002 // (1 + N) if full else 140002
+    if scheme == "texels":
+        res = (8, 8, 4, 2) if C == 8 else (4, 4, 2, 2)  # C = 8: pair buffers and the coarse scatter
+        tree, mlp, bt = tiny_problem(seed=21, B=B, N=N, n_attr=n_attr, widths=widths, bias_scale=0.1, C=C, res=res)
+        feat, interp = tree.feat, binding.INTERP_NODE_BILINEAR
+    else:
+        if C == 8:
+            pytest.skip("four channels only")
+        tree, feat, mlp, bt = paper_problem(B, N, n_attr, widths, 21)
+        interp = binding.INTERP_PAPER
+    bt["x"] = points(B)
+    bt["grad_through_rhs"] = full
+    if N == 0:
+        bt["target_override"] = np.random.default_rng(3).uniform(0, 1, (B, 3)).astype(np.float32)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, list(tree.res), C, feat, mlp.W, mlp.b, dtype=dtype,
+                               interp=interp)
+    dev = binding.device_batch(bt)
+    print(f"[case] smallest workspace {scheme} {dtype} {widths} E={n_attr} N={N} full={full}", flush=True)
+    n = binding.residual_workspace_bytes(model.tree, model.mlp, dev, feat=model.work_feat, W=model.work_W)
+    large = model.new_workspace(dev)
+    assert large.numel() > n
+    guarded = torch.full((n + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    one = torch.ones((), dtype=torch.float64, device="cuda")
+
+    def step(ws, backwards=1):
+        outs = binding.residual_fwd(model.tree, model.mlp, dev, ws, feat=model.work_feat, W=model.work_W)
+        binding.profile_begin(256)
+        for _ in range(backwards):
+            g = [[torch.zeros(p.shape, device="cuda") for p in ps] for ps in (model.feat, model.W, model.b)]
+            binding.residual_bwd(model.tree, model.mlp, dev, outs[2], outs[1], one, *g, ws, feat=model.work_feat,
+                                 W=model.work_W)
+        chunks = binding.profile_end()["backward"][1] / backwards
+        assert chunks == (1 if ws is large else 2)
+        return outs, [t.double() for ts in g for t in ts]
+
+    outs1, whole = step(large)
+    for backwards in (1, 2):
+        outs2, halves = step(guarded[:n], backwards)
+        assert all(torch.equal(a, b) for a, b in zip(outs1, outs2))
+        worst = max(float((a - b).norm() / a.norm()) for a, b in zip(whole, halves) if a.norm() > 0)
+        report(f"smallest workspace {scheme} {dtype} {widths} N={N} backwards={backwards}", worst=worst)
+        assert worst <= 2.0 ** -13
+    assert bool((guarded[n:] == 0x5a).all())
+
+
+def test_no_room_for_one_chunk(monkeypatch):
+    """Where the device has no memory for the larger workspace, the model
+    takes the size the library asks for."""
+    tree, mlp, bt = tiny_problem(seed=22, B=1 << 16, N=0)
+    bt["target_override"] = np.random.default_rng(3).uniform(0, 1, (1 << 16, 3)).astype(np.float32)
+    bt["x"] = points(1 << 16)
+    model = binding.OctaOctree(tree.nodes, tree.level_offset, tree.res, tree.C, tree.feat, mlp.W, mlp.b,
+                               dtype=torch.float16)
+    dev = binding.device_batch(bt)
+    n = binding.residual_workspace_bytes(model.tree, model.mlp, dev, feat=model.work_feat, W=model.work_W)
+    empty = torch.empty
+
+    def no_room(size, *a, **kw):
+        if kw.get("dtype") == torch.uint8 and size > n:
+            raise torch.OutOfMemoryError("no room")
+        return empty(size, *a, **kw)
+
+    assert model.new_workspace(dev).numel() > n
+    monkeypatch.setattr(torch, "empty", no_room)
+    print("[case] no room for one chunk", flush=True)
+    assert model.new_workspace(dev).numel() == n and model.workspace(dev).numel() == n
