@@ -1,9 +1,10 @@
 // Backward of the residual step: seeds, the fused recompute + decoder
-// backward kernel, the feature-gradient scatter, and the fixed-order dW/db
+// backward kernel of FP32 decoders and of the 16-bit ones that oo_bwd16.h has
+// no workgroup for, the feature-gradient scatter, and the fixed-order dW/db
 // reduction.
 //
-// One workgroup (8 waves with 16-bit operands, 16 with FP32) handles 64
-// queries at a time:
+// One workgroup of bwd_kernel (8 waves with 16-bit operands, 16 with FP32)
+// handles 64 queries at a time:
 //  1. encode: node indices and octahedral coordinates come from the forward;
 //     one lane per wave for each query (8 or 16), each gathering whole texels
 //     of its levels; h written to the layer-0 activation buffer as
@@ -17,8 +18,9 @@
 // dW/db leave as one partial per workgroup (accumulated over the launches
 // of one backward), reduced in a fixed order later. A separate,
 // high-occupancy kernel scatters w_tap * dh into the FP32 feature gradient
-// tables with hardware float atomics; the caller runs it on a second stream
-// so that it overlaps the next launch of the fused kernel.
+// tables with hardware float atomics. The caller runs it on a second stream,
+// so that it overlaps the next launch of bwd_kernel; after bwd16_kernel, which
+// leaves no room beside it, on the same stream.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -92,8 +94,8 @@ __host__ __device__ inline size_t lds_weight_bytes(int K0, int H, int n_layers, 
 }
 
 
-// Waves per workgroup. The LDS holds one workgroup per CU, and the feature
-// scatter, which runs beside this kernel on a second stream, gets the wave
+// Waves per workgroup of bwd_kernel. The LDS holds one workgroup per CU, and
+// the feature scatter, which runs beside it on a second stream, gets the wave
 // slots the workgroup leaves free. With 16-bit operands 8 waves (two per SIMD,
 // up to 256 registers each, an eighth of the dW tiles per wave) measured
 // faster for the pair than 16 waves of 128 registers. FP32 reads its weights

@@ -3,12 +3,12 @@
 //
 // Every wave carries 16 queries of its own through the whole chain in
 // registers, from the level features that the forward kept and the caller's
-// surface attributes: the hidden layers, then the gradient back through the transposed weights. Only the
-// weight gradients need the workgroup: dW of a layer is contracted over all
-// its queries, each wave owning a block of dW tiles in registers for the
-// whole kernel, so activations and deltas pass through LDS once per layer,
-// two barriers each. The next tile's inputs and seeds are loaded while this
-// one is worked on.
+// surface attributes: the hidden layers, then the gradient back through the
+// transposed weights. Only the weight gradients need the workgroup: dW of a
+// layer is contracted over all its queries, each wave owning a block of dW
+// tiles in registers for the whole kernel, so activations and deltas pass
+// through LDS once per layer, two barriers each. The next tile's inputs and
+// seeds are loaded while this one is worked on.
 //
 // One packed copy of the weights serves both directions. A fragment is kept
 // as two planes of 4 elements per lane (its slots 0-3 and 4-7); the forward
@@ -19,13 +19,13 @@
 // are, into the [neuron][queries] operands of dW.
 //
 // Bound by LDS reads and the two barriers per layer; the matrix cores are a
-// third busy. 262,144 queries, 88 features, two 128-wide hidden layers in FP16:
-// 96 us, where one kernel that shared 64 queries between its waves and gathered
-// the features again took 335 us; 32,768 queries, 48 inputs, four 128-wide
-// layers: 63 us after 403 us. A bias sum needs
-// an accumulator of its own per layer: one shared by all layers, a column
-// each, is 1% faster but lets an infinite delta of one layer make the others'
-// sums NaN (zero times infinity).
+// third busy. 262,144 queries, 88 features, two 128-wide hidden layers in
+// FP16: 96 us, where one kernel that shared 64 queries between its waves and
+// gathered the features again took 335 us; 32,768 queries, 48 inputs, four
+// 128-wide layers: 63 us after 403 us. A bias sum needs an accumulator of its
+// own per layer: one shared by all layers, a column each, is 1% faster but
+// lets an infinite delta of one layer make the others' sums NaN (zero times
+// infinity).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

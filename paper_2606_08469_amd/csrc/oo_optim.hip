@@ -45,10 +45,10 @@ __device__ inline void adam_quad(const AdamArgs& A, int64_t tq) {
 // copy. The masters, moments and gradients are as good as gone from the
 // caches when they are next read, so their loads and stores bypass them, and
 // each workgroup takes 256 quads and ends instead of looping. 262 million
-// elements (8.9 GB): 1571 us, 5.7 TB/s (1679 if the working copy is stored
-// through the caches); without the cache bypass 1761, looping
-// over 16,384 workgroups 1868, neither (and a search of the segments and a
-// 64-bit division per thread) 2112.
+// elements (8.9 GB) take 1.61 ms, 5.5 TB/s. With one quad per thread: 1571 us
+// (1679 if the working copy is stored through the caches); without the cache
+// bypass 1761, looping over 16,384 workgroups 1868, neither (and a search of
+// the segments and a 64-bit division per thread) 2112.
 // A workgroup has two waves, each thread two quads one after the other: where
 // few maps were read, the time goes to starting waves that find nothing to do
 // (the same elements, a thousandth of them read: 156 us; with four waves of
