@@ -347,7 +347,7 @@ def residual_workspace_bytes(tree: Tree, mlp: MLP, batch: dict, feat=None, W=Non
 
 def _workspace(tree: Tree, mlp: MLP, batch: dict, feat=None, W=None):
     """A workspace of the size the library asks for or, where it makes the
-    backward faster and there is memory for it, large enough for one chunk."""
+    backward faster and there is plenty of memory, large enough for one chunk."""
     n = residual_workspace_bytes(tree, mlp, batch, feat=feat, W=W)
     W = mlp.W if W is None else W
     B, N = batch["x"].shape[0], 0 if batch.get("target_override") is not None else int(batch.get("N", 0))
@@ -355,7 +355,8 @@ def _workspace(tree: Tree, mlp: MLP, batch: dict, feat=None, W=None):
     Qb = Qf if batch.get("grad_through_rhs") else B
     kept = 2 * tree.n_levels * tree.C * Qb
     kept_by_forward = W[0].element_size() == 2 and not (len(W) == 5 and W[0].shape[0] == 128 and W[0].shape[1] > 96)
-    if kept_by_forward and tree.disparity is None and Qb >= 1 << 16 and kept > 20 * Qf - 4 * Qb:
+    if (kept_by_forward and tree.disparity is None and Qb >= 1 << 16 and kept > 20 * Qf - 4 * Qb
+            and 16 * kept <= torch.cuda.mem_get_info()[0]):  # (what the caller allocates later has to fit as before)
         try:
             return torch.empty(n + kept, dtype=torch.uint8, device="cuda")
         except torch.OutOfMemoryError:

@@ -212,3 +212,9 @@ def test_no_room_for_one_chunk(monkeypatch):
     monkeypatch.setattr(torch, "empty", no_room)
     print("[case] no room for one chunk", flush=True)
     assert model.new_workspace(dev).numel() == n and model.workspace(dev).numel() == n
+    monkeypatch.undo()  # and where the rest of the program may need it
+    free, total = torch.cuda.mem_get_info()
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda: (16 * n, total))
+    assert model.new_workspace(dev).numel() > n
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda: (n, total))
+    assert model.new_workspace(dev).numel() == n
