@@ -26,8 +26,8 @@ def points(B):
 def test_many_tiles_per_workgroup(widths, n_attr, dtype):
     """Four- and eight-wave workgroups, exchange buffers for all waves or a
     share of them, and the decoder whose weights are read from L2 (four chunks,
-    its scatter on a second stream), over 2 * 256 * 256 + 34 points: two chunks
-    of two or four tiles per workgroup and a ragged one (or four of two).
+    its scatter on a second stream), over 2 * 256 * 256 + 34 points: one chunk
+    of four or eight tiles per workgroup and a ragged one (or four of two).
     Weight, bias and summed feature gradients against plain FP64 torch that
     rounds inputs, activations, seeds and deltas to 16 bits where the kernel
     does. What is left is FP32 sums that round to the other 16-bit neighbour,
@@ -85,8 +85,8 @@ def paper_problem(B, N, n_attr, widths, seed):
                                                  (torch.float16, (128,) * 4, 112)])
 @pytest.mark.parametrize("N,full", [(0, 0), (1, 1)])
 def test_chunks_add_up(scheme, dtype, widths, n_attr, N, full):
-    """Gradients of 140,002 backward queries (two chunks, or four with the
-    scatter on a second stream) against the same points in batches of at most
+    """Gradients of 140,002 backward queries (one chunk, or four with the
+    scatter on a second stream; test_smallest_workspace has the two) against the same points in batches of at most
     30,000 backward queries, which run in one chunk each and add up weighted
     by their points; with the gradient through the target the secondary
     queries' attributes come from the second array. Each query's terms are the
